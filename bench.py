@@ -36,7 +36,7 @@ COUNTERS_FILE = os.path.join(ROOT, "profiles", "step_kernel_counters.json")
 # per lattice: populations per node, the sources its step kernel is built from,
 # and the committed counter summary of that kernel
 LATTICES = {
-    "d2q9": {"q": 9, "sources": ("lbvp_kernels.hip", "lbvp_device.h", "lbvp_internal.h"),
+    "d2q9": {"q": 9, "sources": ("lbvp_step.h", "lbvp_node.h", "lbvp_device.h", "lbvp_internal.h"),
              "counters": COUNTERS_FILE},
     "d3q19": {"q": 19, "sources": ("lbvp3_kernels.hip", "lbvp_device.h", "lbvp3_internal.h"),
               "counters": os.path.join(ROOT, "profiles", "step3_kernel_counters.json")},

@@ -178,6 +178,17 @@ struct ConvArgs {
 // nodes per thread of the vector form of the step for a storage type (16 bytes)
 int vector_width(int32_t storage);
 
+// The step launches of one storage type (lbvp_step.h, a translation unit each):
+// one domain, or every member of a batch in one launch; moving: the kernels that
+// evaluate a moving mask.
+template <typename S>
+struct StepLaunch {
+    static hipError_t one(bool moving, int32_t mode, bool record, bool fields, const void* src, void* dst,
+                          const void* step_args, hipStream_t s);
+    static hipError_t batch(bool moving, int32_t vec, int32_t block, int32_t mode, bool record, bool fields,
+                            const BatchLaunch& b, hipStream_t s);
+};
+
 // launchers (lbvp_kernels.hip); all return the launch status
 hipError_t launch_step(int32_t storage, int32_t mode, bool record, bool fields, const void* src, void* dst,
                        const void* step_args, hipStream_t s);
