@@ -14,6 +14,7 @@
 
 #include "lbvp3.h"
 #include "lbvp3_internal.h"
+#include "lbvp_readback.h"
 #include "lbvp_graph.h"
 
 using namespace lbvp3;
@@ -183,6 +184,7 @@ Layout3 make_layout(const lbvp3_params& p)
 }  // namespace
 
 struct lbvp3_ctx {
+    lbvp::ReadbackUser readback;
     lbvp3_params p{};
     Layout3 L;
     Launch3 launch;
@@ -760,23 +762,15 @@ lbvp_status lbvp3_read_fields(lbvp3_ctx* c, int32_t z0, int32_t n_planes, double
     if (bad_range(c, z0, n_planes)) return c->fail(LBVP_E_ARG, "plane range outside the grid");
     if (!c->fields_valid) return c->fail(LBVP_E_STATE, "no fields kept since the last init");
     const lbvp3_params& p = c->p;
-    const size_t rs = c->rsize();
-    const size_t rows = (size_t)n_planes * p.ny, n = rows * p.nx;
-    std::vector<char> tmp(std::max<size_t>(n, 1) * rs);
+    const int64_t rows = (int64_t)n_planes * p.ny;
+    LBVP3_HIP(c, hipStreamSynchronize(c->stream));
+    double* dst[7];
+    int64_t off[7];
     for (int f = 0; f < 7; ++f) {
-        const char* srcp = c->at<char>(c->L.fields) + ((size_t)f * c->L.plane_f + (size_t)z0 * p.ny * c->L.pitch) * rs;
-        if (n) {
-            LBVP3_HIP(c, hipMemcpy2DAsync(tmp.data(), (size_t)p.nx * rs, srcp, (size_t)c->L.pitch * rs,
-                                          (size_t)p.nx * rs, rows, hipMemcpyDeviceToHost, c->stream));
-        }
-        LBVP3_HIP(c, hipStreamSynchronize(c->stream));
-        double* dst = out + (size_t)f * n;
-        if (c->is_f64()) std::memcpy(dst, tmp.data(), n * sizeof(double));
-        else {
-            const float* v = reinterpret_cast<const float*>(tmp.data());
-            for (size_t k = 0; k < n; ++k) dst[k] = (double)v[k];
-        }
+        dst[f] = out + (size_t)f * (size_t)rows * p.nx;
+        off[f] = f * c->L.plane_f + (int64_t)z0 * p.ny * c->L.pitch;
     }
+    LBVP3_HIP(c, lbvp::read_planes(c->stream, c->is_f64(), c->at<char>(c->L.fields), off, 7, c->L.pitch, p.nx, rows, dst));
     return LBVP_OK;
 }
 

@@ -22,6 +22,7 @@
 #include "lbvp.h"
 #include "lbvp_graph.h"
 #include "lbvp_internal.h"
+#include "lbvp_readback.h"
 
 using namespace lbvp;
 using lbvp_host::GraphCache;
@@ -286,6 +287,7 @@ class PinnedRing {
 }  // namespace
 
 struct lbvp_ctx {
+    ReadbackUser readback;
     lbvp_params p{};
     Layout L;
     hipStream_t stream = nullptr;
@@ -1473,22 +1475,16 @@ lbvp_status lbvp_read_fields_rows(lbvp_ctx* c, int32_t y0, int32_t n_rows, doubl
     if (y0 < 0 || n_rows < 1 || n_rows > p.ny - y0) return c->fail(LBVP_E_ARG, "row range outside the grid");
     if (!c->fields_valid) return c->fail(LBVP_E_STATE, "no fields kept since the last init");
     LBVP_HIP(c, hipStreamSynchronize(c->stream));
-    double* dst[5] = {rho, ux, uy, fx, fy};
-    const size_t rs = c->rsize();
-    const size_t n = (size_t)p.nx * n_rows;
-    std::vector<char> tmp(n * rs);
+    double* planes[5] = {rho, ux, uy, fx, fy};
+    double* dst[5];
+    int64_t off[5];
+    int n = 0;
     for (int q = 0; q < 5; ++q) {
-        if (!dst[q]) continue;
-        const char* srcp = c->at<char>(c->L.fields) + ((size_t)q * c->L.plane_f + (size_t)y0 * c->L.pitch) * rs;
-        LBVP_HIP(c, hipMemcpy2DAsync(tmp.data(), (size_t)p.nx * rs, srcp, (size_t)c->L.pitch * rs,
-                                     (size_t)p.nx * rs, (size_t)n_rows, hipMemcpyDeviceToHost, c->stream));
-        LBVP_HIP(c, hipStreamSynchronize(c->stream));
-        if (c->is_f64()) std::memcpy(dst[q], tmp.data(), n * sizeof(double));
-        else {
-            const float* f = reinterpret_cast<const float*>(tmp.data());
-            for (size_t k = 0; k < n; ++k) dst[q][k] = (double)f[k];
-        }
+        if (!planes[q]) continue;
+        dst[n] = planes[q];
+        off[n++] = q * c->L.plane_f + (int64_t)y0 * c->L.pitch;
     }
+    LBVP_HIP(c, read_planes(c->stream, c->is_f64(), c->at<char>(c->L.fields), off, n, c->L.pitch, p.nx, n_rows, dst));
     return LBVP_OK;
 }
 
