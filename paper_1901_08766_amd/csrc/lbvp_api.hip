@@ -220,7 +220,7 @@ Layout make_layout(const lbvp_params* p)
     L.body_slots = take((size_t)L.slot_cap * sizeof(int32_t));
     L.ring_force = take((size_t)L.capacity * L.max_bodies * 2 * sizeof(double));
     L.ring_mass = take((size_t)L.capacity * sizeof(double));
-    L.rec_count = take(sizeof(int64_t));
+    L.rec_count = take(FIN_COUNTERS * sizeof(int64_t));
     L.ghost_w = take(3 * (size_t)p->ny * es);
     L.ghost_e = take(3 * (size_t)p->ny * es);
     L.stage = take(stage_bytes);
@@ -649,7 +649,7 @@ lbvp_status pose_window(lbvp_ctx* c, int64_t next, int64_t n)
     for (int32_t r = 0; r < POSE_ROWS; ++r) moving_pose(c, next + r, c->pose_host.data() + r * row);
     LBVP_HIP(c, hipMemcpyAsync(c->at<double>(c->L.pose), c->pose_host.data(), c->pose_host.size() * sizeof(double),
                                hipMemcpyHostToDevice, c->stream));
-    LBVP_HIP(c, launch_set_i64(c->at<int64_t>(c->L.pose_base), 0, c->stream));
+    LBVP_HIP(c, launch_set_i64(c->at<int64_t>(c->L.pose_base), 1, 0, c->stream));
     c->pose_first = next;
     // the force slots of the window's reach (after the previous run's last
     // record was summed: same stream)
@@ -914,7 +914,8 @@ lbvp_status batch_run(lbvp_batch* b, int64_t step0, int64_t k0, int64_t n, bool 
         L.part_buf = (int32_t)(*recs & 1);
         L.fin_buf = pending ? pending_buf : -1;
         L.n_domains = (int32_t)b->members.size();
-        L.n_fin = L.fin_buf >= 0 ? (L.n_domains + N_XCD - 1) / N_XCD * N_XCD : 0;
+        L.fin_share = batch_fin_share(L.n_domains);
+        L.n_fin = L.fin_buf >= 0 ? (L.n_domains * L.fin_share + N_XCD - 1) / N_XCD * N_XCD : 0;
         L.pose_k = (int32_t)(k - k0);
         if (!b->halo_w.empty()) {   // the cuts' halo columns for this step
             BatchHalo H{};
@@ -1347,7 +1348,7 @@ lbvp_status lbvp_init_equilibrium(lbvp_ctx* c, const double* rho, const double* 
         LBVP_HIP(c, launch_init(p.storage, c->at<char>(L.lat[0]), c->at<char>(L.fields), a, s));
     }
     LBVP_HIP(c, refresh_aa_ghosts(c));
-    LBVP_HIP(c, launch_set_i64(c->fin.rec_count, 0, s));
+    LBVP_HIP(c, launch_set_i64(c->fin.rec_count, FIN_COUNTERS, 0, s));
     LBVP_HIP(c, hipStreamSynchronize(s));
     c->cur = 0;
     c->step = 0;
@@ -1658,7 +1659,7 @@ lbvp_status lbvp_load_state(lbvp_ctx* c, const void* buf, size_t size)
     LBVP_HIP(c, hipMemcpyAsync(c->at<char>(c->L.ghost_w), gw, h.ghost_bytes, hipMemcpyHostToDevice, s));
     LBVP_HIP(c, hipMemcpyAsync(c->at<char>(c->L.ghost_e), ge, h.ghost_bytes, hipMemcpyHostToDevice, s));
     LBVP_HIP(c, hipMemcpyAsync(c->at<char>(c->L.fields), fields, h.field_bytes, hipMemcpyHostToDevice, s));
-    LBVP_HIP(c, launch_set_i64(c->fin.rec_count, h.records, s));
+    LBVP_HIP(c, launch_set_i64(c->fin.rec_count, FIN_COUNTERS, h.records, s));
     LBVP_HIP(c, hipStreamSynchronize(s));
     c->graphs.clear(s);
     c->cur = h.cur;

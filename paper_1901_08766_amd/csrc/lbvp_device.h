@@ -338,12 +338,12 @@ __device__ __forceinline__ void store_vec_shifted(S* p, const S (&in)[V])
 }
 
 // ------------------------------------------------------------ the record --
-// One block sums one force record (see FinalizeArgs) in an order fixed by the
-// data alone: the partials are dealt to FIN_LANES virtual lanes (lane v takes
-// v, v + FIN_LANES, ...), each lane adds its share with eight interleaved
-// accumulators (so that loads overlap), and the lanes meet in a fixed binary
-// tree in LDS. Neither the block size of the launch that runs it nor the way
-// steps are split over calls changes a record by one bit.
+// A force record is summed in an order fixed by the data alone: the partials are
+// dealt to FIN_LANES virtual lanes (lane v takes v, v + FIN_LANES, ...), each
+// lane adds its share with eight interleaved accumulators (so that loads
+// overlap), and the lanes meet in a fixed binary tree. Neither the block size of
+// the launch that runs it nor the way steps are split over calls changes a
+// record by one bit.
 constexpr int FIN_LANES = 256;
 
 __device__ __forceinline__ double lane_sum(const double* x, int n, int v)
@@ -354,10 +354,12 @@ __device__ __forceinline__ double lane_sum(const double* x, int n, int v)
 #pragma unroll
         for (int u = 0; u < 8; ++u) acc[u] += x[k + u * FIN_LANES];
     }
+    if (k < n) {   // at most 7 left, all loaded at once (past the end: the last one, counted as 0)
+        double y[7];
 #pragma unroll
-    for (int u = 0; u < 7; ++u) {   // at most 7 left
-        const int kk = k + u * FIN_LANES;
-        if (kk < n) acc[u] += x[kk];
+        for (int u = 0; u < 7; ++u) y[u] = x[min(k + u * FIN_LANES, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 7; ++u) acc[u] += k + u * FIN_LANES < n ? y[u] : 0.0;
     }
     return ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
 }

@@ -26,6 +26,7 @@ constexpr int MAX_TILE_BAND = 1 << 16;
 // remainder of at most 1/2, at any coordinate below 2^24.
 constexpr int BODY_STRIDE = 7;
 constexpr int FIN_THREADS = 256;
+constexpr int FIN_COUNTERS = 8;     // record counters of a context: most blocks that share one record's sums
 constexpr int MAX_MOVING = 8;       // bodies of a domain with moving masks
 constexpr int POSE_STRIDE = 8;      // doubles per body pose row
 constexpr int POSE_ROWS = 1024;     // time levels per uploaded pose table
@@ -50,7 +51,7 @@ struct FinalizeArgs {
     int64_t slot_stride, mass_stride;
     double* ring_force;             // [capacity][max_bodies][2]
     double* ring_mass;              // [capacity]
-    int64_t* rec_count;             // records written so far
+    int64_t* rec_count;             // [FIN_COUNTERS] records written so far, all equal between launches
 };
 
 template <typename R>
@@ -116,8 +117,9 @@ struct BatchLaunch {
     int32_t flip;                   // lattice parity of this step relative to StepArgs::cur
     int32_t part_buf, fin_buf;      // as in StepArgs, for every domain of the batch
     int32_t n_domains;
-    int32_t n_fin;                  // leading blocks that sum the fin_buf records: n_domains
+    int32_t n_fin;                  // leading blocks that sum the fin_buf records: n_domains * fin_share
                                     // rounded up to a multiple of 8, or 0 if fin_buf < 0
+    int32_t fin_share;              // leading blocks per domain
     int32_t pose_k;                 // this launch's step within the run (moving bodies)
     int32_t off32;                  // every member's StepArgs::off32
     const int32_t* tile_domain;     // [total_tiles] domain of each tile
@@ -203,11 +205,13 @@ hipError_t launch_step_batch(int32_t storage, int32_t vec, int32_t block, int32_
 hipError_t launch_pose_advance(int64_t* base, int64_t n, hipStream_t s);
 hipError_t launch_pose_advance_batch(int32_t storage, const void* args, int32_t n_domains, int64_t n, hipStream_t s);
 hipError_t launch_finalize_batch(const FinalizeArgs* fin_dev, int32_t n, int32_t buf, hipStream_t s);
+// leading blocks per domain of a batch of n domains
+int32_t batch_fin_share(int32_t n);
 hipError_t launch_finalize(const FinalizeArgs& a, int32_t buf, hipStream_t s);
 hipError_t launch_init(int32_t storage, void* lat, void* fields, const ConvArgs& a, hipStream_t s);
 hipError_t launch_decode(int32_t storage, const void* lat, const ConvArgs& a, hipStream_t s);
 hipError_t launch_encode(int32_t storage, void* lat, const ConvArgs& a, hipStream_t s);
-hipError_t launch_set_i64(int64_t* p, int64_t v, hipStream_t s);
+hipError_t launch_set_i64(int64_t* p, int32_t n, int64_t v, hipStream_t s);   // p[0 .. n - 1] = v, n <= 64
 hipError_t launch_copy16(const void* src, void* dst, int64_t n16, hipStream_t s);
 hipError_t launch_halo(int32_t storage, const HaloArgs& h, hipStream_t s);
 hipError_t launch_halo_batch(int32_t storage, const BatchHalo& h, hipStream_t s);

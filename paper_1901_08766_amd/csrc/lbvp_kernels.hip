@@ -17,14 +17,15 @@ namespace {
 __global__ void __launch_bounds__(FIN_THREADS) k_finalize(FinalizeArgs a, int32_t buf)
 {
     __shared__ double lds[2 * FIN_LANES];
-    finalize_record(a, buf, lds);
+    finalize_record(a, buf, (int)blockIdx.x, FIN_COUNTERS, lds);
 }
 
-// The same for every domain of a batch, one block each.
-__global__ void __launch_bounds__(FIN_THREADS) k_finalize_batch(const FinalizeArgs* fins, int32_t buf)
+// The same for every domain of a batch.
+__global__ void __launch_bounds__(FIN_THREADS) k_finalize_batch(const FinalizeArgs* fins, int32_t share, int32_t buf)
 {
     __shared__ double lds[2 * FIN_LANES];
-    finalize_record(fins[blockIdx.x], buf, lds);
+    const int d = (int)blockIdx.x / share;
+    finalize_record(fins[d], buf, (int)blockIdx.x - d * share, share, lds);
 }
 
 // Moving bodies: after a run of n steps, the pose table row of the next step.
@@ -100,7 +101,7 @@ __global__ void __launch_bounds__(256) k_encode(S* lat, ConvArgs a)
         lat[(a.swap ? OPP_ALL[q] : q) * a.plane + lo] = enc<S>((R)(a.pops[q * n + k] / W_ALL[q] - a.rho0));
 }
 
-__global__ void k_set_i64(int64_t* p, int64_t v) { *p = v; }
+__global__ void k_set_i64(int64_t* p, int64_t v) { p[threadIdx.x] = v; }
 
 // A plain device copy: one 16-byte non-temporal load and store per thread in
 // 64-thread blocks, the fastest of the copy forms measured (6.6-6.7 TB/s against
@@ -244,9 +245,14 @@ hipError_t launch_pose_advance_batch(int32_t storage, const void* args, int32_t 
     return hipGetLastError();
 }
 
+// Few domains: their launches are short, so a record's sums run side by side
+// (as for a single domain); many domains already spread theirs over the chip.
+int32_t batch_fin_share(int32_t n) { return n <= 16 ? 4 : n <= 64 ? 2 : 1; }
+
 hipError_t launch_finalize_batch(const FinalizeArgs* fin_dev, int32_t n, int32_t buf, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize_batch, dim3((unsigned)n), dim3(FIN_THREADS), 0, s, fin_dev, buf);
+    const int32_t share = batch_fin_share(n);
+    hipLaunchKernelGGL(k_finalize_batch, dim3((unsigned)(n * share)), dim3(FIN_THREADS), 0, s, fin_dev, share, buf);
     return hipGetLastError();
 }
 
@@ -265,7 +271,7 @@ hipError_t launch_aa_ghosts(int32_t storage, const void* lat, const GhostArgs& a
 
 hipError_t launch_finalize(const FinalizeArgs& a, int32_t buf, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FIN_THREADS), 0, s, a, buf);
+    hipLaunchKernelGGL(k_finalize, dim3(FIN_COUNTERS), dim3(FIN_THREADS), 0, s, a, buf);
     return hipGetLastError();
 }
 
@@ -345,9 +351,9 @@ hipError_t launch_halo_batch(int32_t storage, const BatchHalo& h, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_set_i64(int64_t* p, int64_t v, hipStream_t s)
+hipError_t launch_set_i64(int64_t* p, int32_t n, int64_t v, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_set_i64, dim3(1), dim3(1), 0, s, p, v);
+    hipLaunchKernelGGL(k_set_i64, dim3(1), dim3((unsigned)n), 0, s, p, v);
     return hipGetLastError();
 }
 

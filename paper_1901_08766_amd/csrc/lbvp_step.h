@@ -462,10 +462,10 @@ __global__ void __launch_bounds__(256)
 k_step(const S* __restrict__ src, S* __restrict__ dst, StepArgs<typename Arith<S>::R> a)
 {
     __shared__ double lds[2 * FIN_LANES];   // the record sums, then the per-wavefront sums
-    // block 0 of the first 8 sums the previous step's record (no block waits on it)
+    // the first 8 blocks sum the previous step's record (no block waits on them)
     const int lead = a.fin_buf >= 0 ? N_XCD : 0;
     if ((int)blockIdx.x < lead) {
-        if (blockIdx.x == 0) finalize_record(a.fin, a.fin_buf, lds);
+        finalize_record(a.fin, a.fin_buf, (int)blockIdx.x, N_XCD, lds);
         return;
     }
     const int t = xcd_tile(a.tiles_per_xcd, a.band_log2, lead);
@@ -480,7 +480,7 @@ __global__ void __launch_bounds__(256) k_step_aa(S* lat, StepArgs<typename Arith
     __shared__ double lds[2 * FIN_LANES];
     const int lead = a.fin_buf >= 0 ? N_XCD : 0;
     if ((int)blockIdx.x < lead) {
-        if (blockIdx.x == 0) finalize_record(a.fin, a.fin_buf, lds);
+        finalize_record(a.fin, a.fin_buf, (int)blockIdx.x, N_XCD, lds);
         return;
     }
     const int t = xcd_tile(a.tiles_per_xcd, a.band_log2, lead);
@@ -497,11 +497,13 @@ __global__ void __launch_bounds__(256) k_step_batch(BatchLaunch b)
     using R = typename Arith<S>::R;
     __shared__ double lds[2 * FIN_LANES];
     const StepArgs<R>* args = static_cast<const StepArgs<R>*>(b.args);
-    // the first n_fin blocks sum the previous step's record of one domain each:
-    // dispatched first and spread over the XCDs, they overlap the streaming
-    // tiles instead of trailing them (n_fin is a multiple of 8)
+    // the first n_fin blocks sum the domains' previous records, fin_share blocks
+    // per domain: dispatched first and spread over the XCDs, they overlap the
+    // streaming tiles instead of trailing them (n_fin is a multiple of 8)
     if ((int)blockIdx.x < b.n_fin) {
-        if ((int)blockIdx.x < b.n_domains) finalize_record(args[blockIdx.x].fin, b.fin_buf, lds);
+        const int d = (int)blockIdx.x / b.fin_share;
+        if (d < b.n_domains)
+            finalize_record(args[d].fin, b.fin_buf, (int)blockIdx.x - d * b.fin_share, b.fin_share, lds);
         return;
     }
     const int g = xcd_tile(b.tiles_per_xcd, b.band_log2, b.n_fin);
