@@ -175,7 +175,7 @@ Layout3 make_layout(const lbvp3_params& p)
     L.ring_mass = take((size_t)L.capacity * 8);
     L.rec_count = take(8);
     L.arrivals = take(8);
-    L.fin_stage = take((size_t)N_LEAD * (1 + 3 * L.max_bodies) * 8);
+    L.fin_stage = take(2 * (size_t)N_SLICES * (1 + 3 * L.max_bodies) * 8);   // double-buffered
     L.stage = take((size_t)L.stage_planes * plane_pops);
     L.total = off;
     return L;
@@ -192,8 +192,6 @@ struct lbvp3_ctx {
     char* mem = nullptr;
     int cur = 0;
     int64_t step = 0, rec_head = 0, rec_tail = 0;
-    bool pending = false;       // a recorded step whose sums are not yet in the ring
-    int32_t pending_buf = 0;
     bool fields_valid = false;
     int32_t n_bodies = 0;
     double tau_minus = 0.0;
@@ -323,8 +321,26 @@ void fill_args(lbvp3_ctx* c, Step3Args<R>& a)
     a.fields = c->at<R>(L.fields);
     a.part_buf = 0;
     a.fin_buf = -1;
+    a.fin_stage = 0;
+    a.add_stage = -1;
     a.fin = c->fin;
 }
+
+// The records a run of steps still has to sum: the last recording step's
+// partials and the stage rows of the record before (see Fin3Args). Every run
+// starts and ends with none.
+struct RunRecords {
+    int32_t part = -1;    // partial buffer whose slices come next, or -1
+    int32_t stage = 0;    // stage buffer those slice sums go to
+    int32_t rows = -1;    // stage buffer whose rows are added next, or -1
+    // a step was launched that did both, and itself recorded into partial buffer buf (or -1)
+    void stepped(int32_t buf)
+    {
+        rows = part >= 0 ? stage : -1;
+        if (part >= 0) stage ^= 1;
+        part = buf;
+    }
+};
 
 // The (tile, body) tables for the current tiling and mask: a slot per body
 // present in each tile, numbered in tile order, and the slots of each body.
@@ -519,7 +535,8 @@ lbvp_status lbvp3_create(const lbvp3_params* p, void* hip_stream, lbvp3_ctx** ou
     c->fin.ring_mass = c->at<double>(L.ring_mass);
     c->fin.rec_count = c->at<int64_t>(L.rec_count);
     c->fin.arrivals = c->at<int64_t>(L.arrivals);
-    c->fin.stage = c->at<double>(L.fin_stage);
+    for (int k = 0; k < 2; ++k)
+        c->fin.stage[k] = c->at<double>(L.fin_stage) + (size_t)k * N_SLICES * (1 + 3 * L.max_bodies);
     c->launch = default_launch(*p);
     c->mask_host.assign((size_t)L.rows * p->nx, 0);
     lbvp_status s = lbvp3_set_mask(c, c->mask_host.data(), 0, nullptr);
@@ -609,7 +626,6 @@ lbvp_status lbvp3_init_equilibrium(lbvp3_ctx* c, const double* rho, const double
     c->cur = 0;
     c->step = 0;
     c->rec_head = c->rec_tail = 0;
-    c->pending = false;
     c->fields_valid = true;
     return LBVP_OK;
 }
@@ -631,29 +647,28 @@ lbvp_status lbvp3_step(lbvp3_ctx* c, int64_t n_steps, uint32_t flags)
     c->a32.fin = c->fin;
     // n steps, the last keeping the fields if asked, and the call's last record summed
     auto enqueue = [&](int64_t n, bool keep_last) -> lbvp_status {
+        RunRecords rr;
         for (int64_t k = 0; k < n; ++k) {
             const int64_t next = c->step + 1;
             const bool record = fe > 0 && next % fe == 0;
             const bool keep_here = keep_last && k == n - 1;
             const int32_t part_buf = (int32_t)(c->rec_head & 1);
             c->a64.part_buf = c->a32.part_buf = part_buf;
-            c->a64.fin_buf = c->a32.fin_buf = c->pending ? c->pending_buf : -1;
+            c->a64.fin_buf = c->a32.fin_buf = rr.part;
+            c->a64.fin_stage = c->a32.fin_stage = rr.stage;
+            c->a64.add_stage = c->a32.add_stage = rr.rows;
             hipError_t e = launch_step3(c->p.storage, record, keep_here, c->at<char>(c->L.lat[c->cur]),
                                         c->at<char>(c->L.lat[c->cur ^ 1]), args, c->stream);
             if (e != hipSuccess) return c->hip_fail(e, "step kernel launch");
-            c->pending = record;
-            if (record) {
-                c->pending_buf = part_buf;
-                c->rec_head += 1;
-            }
+            rr.stepped(record ? part_buf : -1);
+            if (record) c->rec_head += 1;
             if (keep_here) c->fields_valid = true;
             c->cur ^= 1;
             c->step = next;
         }
-        if (c->pending) {   // the last record of the call is summed on its own
-            hipError_t e = launch_finalize3(c->fin, c->pending_buf, c->stream);
+        if (rr.part >= 0 || rr.rows >= 0) {   // the last records of the run are summed on their own
+            hipError_t e = launch_finalize3(c->fin, rr.part, rr.stage, rr.rows, c->stream);
             if (e != hipSuccess) return c->hip_fail(e, "finalize kernel launch");
-            c->pending = false;
         }
         return LBVP_OK;
     };
@@ -679,21 +694,16 @@ lbvp_status lbvp3_step(lbvp3_ctx* c, int64_t n_steps, uint32_t flags)
             c->cur = (int)((cur0 + n) & 1);
             c->step = step0 + n;
             c->rec_head = head0 + recs;
-            c->pending = false;
-            if (recs > 0) c->pending_buf = (int32_t)((c->rec_head - 1) & 1);
             if (keep_here) c->fields_valid = true;
         } else {
             const int cur0 = c->cur;
             const int64_t step0 = c->step, head0 = c->rec_head;
-            const bool pend0 = c->pending, fields0 = c->fields_valid;
-            const int32_t buf0 = c->pending_buf;
+            const bool fields0 = c->fields_valid;
             auto restore = [&]() {
                 c->cur = cur0;
                 c->step = step0;
                 c->rec_head = head0;
-                c->pending = pend0;
                 c->fields_valid = fields0;
-                c->pending_buf = buf0;
             };
             LBVP3_HIP(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
             const lbvp_status st = enqueue(n, keep_here);
@@ -933,7 +943,6 @@ lbvp_status lbvp3_load_state(lbvp3_ctx* c, const void* buf, size_t size)
     c->cur = h.cur;
     c->step = h.step;
     c->rec_head = c->rec_tail = h.records;
-    c->pending = false;
     c->fields_valid = h.fields_valid != 0;
     return LBVP_OK;
 }
@@ -1063,6 +1072,7 @@ lbvp_status lbvp3_batch_step(lbvp3_batch* b, int64_t n_steps, uint32_t flags)
     // steps k0 .. k0 + n - 1 of the call (the members' parity flips with k),
     // then the run's last record summed in one launch
     auto run = [&](int64_t k0, int64_t n_run, bool keep_last) -> lbvp_status {
+    RunRecords rr;
     for (int64_t k = k0; k < k0 + n_run; ++k) {
         const int64_t next = c0->step + 1;
         const bool record = fe > 0 && next % fe == 0;
@@ -1070,26 +1080,27 @@ lbvp_status lbvp3_batch_step(lbvp3_batch* b, int64_t n_steps, uint32_t flags)
         const int32_t part_buf = (int32_t)(c0->rec_head & 1);
         L.flip = (int32_t)(k & 1);
         L.part_buf = part_buf;
-        L.fin_buf = c0->pending ? c0->pending_buf : -1;
-        L.n_fin = L.fin_buf >= 0 ? (n + N_XCD - 1) / N_XCD * N_XCD : 0;
+        L.fin_buf = rr.part;
+        L.fin_stage = rr.stage;
+        L.add_stage = rr.rows;
+        L.n_fin = rr.part >= 0 ? slice_blocks(n, b->block) : 0;
+        L.n_add = rr.rows >= 0 ? (n + N_XCD - 1) / N_XCD * N_XCD : 0;
         e = launch_step3_batch(b->storage, b->vec, b->block, record, keep_here, L, b->stream);
         if (e != hipSuccess) return b->hip_fail(e, "batch step kernel launch");
+        rr.stepped(record ? part_buf : -1);
         for (lbvp3_ctx* c : b->members) {
-            c->pending = record;
-            if (record) {
-                c->pending_buf = part_buf;
-                c->rec_head += 1;
-            }
+            if (record) c->rec_head += 1;
             if (keep_here) c->fields_valid = true;
             c->cur ^= 1;
             c->step = next;
         }
     }
-    if (c0->pending) {   // the last record of the run, every member's in one launch
-        L.fin_buf = c0->pending_buf;
+    if (rr.part >= 0 || rr.rows >= 0) {   // the last records of the run, every member's in one launch
+        L.fin_buf = rr.part;
+        L.fin_stage = rr.stage;
+        L.add_stage = rr.rows;
         e = launch_finalize3_members(b->storage, L, b->stream);
         if (e != hipSuccess) return b->hip_fail(e, "finalize kernel launch");
-        for (lbvp3_ctx* c : b->members) c->pending = false;
     }
     return LBVP_OK;
     };
@@ -1119,24 +1130,20 @@ lbvp_status lbvp3_batch_step(lbvp3_batch* b, int64_t n_steps, uint32_t flags)
                 c->cur = (c->cur + (int)(n_run & 1)) & 1;
                 c->step = step0 + n_run;
                 c->rec_head += recs;
-                c->pending = false;
-                if (recs > 0) c->pending_buf = (int32_t)((c->rec_head - 1) & 1);
                 if (keep_here) c->fields_valid = true;
             }
         } else {
-            struct Saved { int cur; int64_t step, head; bool pending, fields; int32_t buf; };
+            struct Saved { int cur; int64_t step, head; bool fields; };
             std::vector<Saved> saved;
             for (lbvp3_ctx* c : b->members)
-                saved.push_back({c->cur, c->step, c->rec_head, c->pending, c->fields_valid, c->pending_buf});
+                saved.push_back({c->cur, c->step, c->rec_head, c->fields_valid});
             auto restore = [&]() {
                 for (size_t i = 0; i < b->members.size(); ++i) {
                     lbvp3_ctx* c = b->members[i];
                     c->cur = saved[i].cur;
                     c->step = saved[i].step;
                     c->rec_head = saved[i].head;
-                    c->pending = saved[i].pending;
                     c->fields_valid = saved[i].fields;
-                    c->pending_buf = saved[i].buf;
                 }
             };
             e = hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal);

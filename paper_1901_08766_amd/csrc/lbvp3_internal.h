@@ -12,7 +12,8 @@ namespace lbvp3 {
 constexpr int Q = 19;
 constexpr int N_XCD = 8;
 constexpr int FIN_THREADS = 256;
-constexpr int N_LEAD = 32;   // blocks that sum one record, a multiple of the 8 XCDs
+constexpr int N_SLICES = 32;       // slices a record's partials are summed in, a wavefront each
+constexpr int FIN_BLOCK_WAVES = 4;  // wavefronts of a block of the record kernels
 constexpr int MAX_TILE_BAND = 1 << 16;
 // Body table row, in the arithmetic type: the centre split into its nearest
 // integer and the remainder (x - c = (x - c_int) - c_frac, exact up to one
@@ -28,11 +29,13 @@ constexpr int CZ[Q] = {0, 0, 0, 0, 0, 1, -1, 0, 0, 0, 0, 1, -1, -1, 1, 1, -1, -1
 
 // Sums one force record: the per-wavefront mass partials and the (tile, body)
 // force partials of partial buffer `buf`, in a fixed order, into ring slot
-// rec_count % capacity. N_LEAD blocks each sum a fixed slice into a row of
-// `stage`; the last to arrive (counted in `arrivals`) adds the rows in block
-// order. The partials are double-buffered so that the record of one step is
-// summed by leading blocks of the next step's launch while that step writes the
-// other buffer.
+// rec_count % capacity, in two stages. First every one of N_SLICES wavefronts
+// sums its fixed slice of the partials into a row of a `stage` buffer, then one
+// block adds the rows in slice order. During a run of steps the two stages of
+// step k's record are done by leading blocks of the launches of steps k + 1 and
+// k + 2, so nothing waits inside a launch; the partials and the stage rows are
+// double-buffered. The last records of a run are summed by a kernel of their
+// own, whose last block to arrive (counted in `arrivals`) adds the rows.
 struct Fin3Args {
     int32_t n_bodies, max_bodies, n_mass;   // n_mass: wavefronts of a step launch
     int64_t capacity;
@@ -45,7 +48,7 @@ struct Fin3Args {
     double* ring_force;             // [capacity][max_bodies][3]
     double* ring_mass;              // [capacity]
     int64_t* rec_count;             // records written so far
-    double* stage;                  // [N_LEAD][1 + 3 max_bodies] slice sums
+    double* stage[2];               // [N_SLICES][1 + 3 max_bodies] slice sums
     int64_t* arrivals;              // slices summed of the record in progress (0 between records)
 };
 
@@ -77,7 +80,9 @@ struct Step3Args {
     double* mass_part;              // [2][fin.mass_stride]
     R* fields;                      // [7][plane_f]
     int32_t part_buf;               // partial buffer a recording step writes
-    int32_t fin_buf;                // partial buffer whose record a leading block sums, or -1
+    int32_t fin_buf;                // partial buffer whose slices leading wavefronts sum, or -1
+    int32_t fin_stage;              // stage buffer those slice sums go to
+    int32_t add_stage;              // stage buffer whose rows a leading block adds to a record, or -1
     Fin3Args fin;
 };
 
@@ -106,14 +111,17 @@ struct Member3 {
 struct Batch3Launch {
     int32_t total_tiles, tiles_per_xcd, band_log2;
     int32_t flip;                   // this step's lattice parity relative to Member3::cur
-    int32_t part_buf, fin_buf;      // as in Step3Args, for every member
+    int32_t part_buf, fin_buf, fin_stage, add_stage;   // as in Step3Args, for every member
     int32_t n_members;
-    int32_t n_fin;                  // leading blocks, one per member (rounded up to a multiple of
-                                    // the 8 XCDs), or 0 if fin_buf < 0
+    int32_t n_fin, n_add;           // leading blocks that sum slices, then those that add rows (one per
+                                    // member): multiples of the 8 XCDs, or 0 with nothing to sum or add
     const int32_t* tile_domain;     // [total_tiles] member of each tile
     const int32_t* tile_start;      // [n_members] first tile of each member
     const void* members;            // Member3<R>[n_members]
 };
+
+// leading blocks of a step launch of `block` threads that sum slices for n members
+constexpr int32_t slice_blocks(int32_t n, int32_t block) { return (n * (N_SLICES / (block / 64)) + 7) / 8 * 8; }
 
 // nodes per thread the step kernel is built for, per storage type
 bool vec_supported(int32_t storage, int32_t vec);
@@ -122,8 +130,10 @@ hipError_t launch_step3(int32_t storage, bool record, bool fields, const void* s
                         hipStream_t s);
 hipError_t launch_step3_batch(int32_t storage, int32_t vec, int32_t block, bool record, bool fields,
                               const Batch3Launch& b, hipStream_t s);
-hipError_t launch_finalize3(const Fin3Args& a, int32_t buf, hipStream_t s);
-// every member's record in partial buffer b.fin_buf summed by one block each
+// what a run of steps leaves to sum: the record whose rows are in stage buffer
+// add_stage (or -1), then the one in partial buffer buf (or -1)
+hipError_t launch_finalize3(const Fin3Args& a, int32_t buf, int32_t stage, int32_t add_stage, hipStream_t s);
+// the same for every member of a batch (b's fin_buf, fin_stage, add_stage)
 hipError_t launch_finalize3_members(int32_t storage, const Batch3Launch& b, hipStream_t s);
 hipError_t launch_init3(int32_t storage, void* lat, void* fields, const Conv3Args& a, hipStream_t s);
 hipError_t launch_decode3(int32_t storage, const void* lat, const Conv3Args& a, hipStream_t s);

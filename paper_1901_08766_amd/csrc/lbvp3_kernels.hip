@@ -58,7 +58,6 @@ using lbvp::Pair;
 using lbvp::recip;
 using lbvp::store_one;
 using lbvp::store_vec;
-using lbvp::tree_sum;
 using lbvp::wave_sum_lane63;
 using lbvp::xcd_tile;
 
@@ -382,171 +381,140 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
     }
 }
 
-// tree_sum's binary tree over FIN_LANES virtual lanes, with the same pairwise
-// additions (lane v takes lane v + w, w = FIN_LANES / 2 .. 1), where thread t
-// holds lanes t + k * blockDim in h[k]: levels w >= blockDim inside each thread,
-// levels 64 <= w < blockDim through lds, the last six by wave shuffles. The sum
-// is bitwise tree_sum's and lands in thread 0 only.
-constexpr int SERIAL_H = FIN_LANES / 64;
-__device__ __forceinline__ double serial_tree(double (&h)[SERIAL_H], double* lds)
+// One wavefront sums slice `part` of a record's partials into its stage row:
+// mass, then the force on each body (one pass over the slice's slots serves
+// three components). The order is fixed by the partials alone, so neither the
+// launch that runs it nor the way steps are split over calls changes a record by
+// one bit: FIN_LANES virtual lanes (thread l takes lanes l, l + 64, l + 128,
+// l + 192) meet pairwise with halving spans, two levels in the thread and six by
+// lane moves. The thread's lanes are taken one after the other (in the tree's
+// order 0, 2, 1, 3, each pair added when complete), so that the sums need no
+// more registers than the step that the kernel is for.
+__device__ __forceinline__ void slice_sums(const Fin3Args& f, int buf, int part, double* row)
 {
-    const int bd = (int)blockDim.x, t = (int)threadIdx.x;
-    const int nh = FIN_LANES / bd;
-#pragma unroll
-    for (int k = SERIAL_H / 2; k > 0; k >>= 1)
-        if (k < nh)
-#pragma unroll
-            for (int i = 0; i < k; ++i) h[i] += h[i + k];
-    for (int w = bd / 2; w >= 64; w >>= 1) {
-        __syncthreads();   // lds free from the previous level or sum
-        if (t >= w && t < 2 * w) lds[t - w] = h[0];
-        __syncthreads();
-        if (t < w) h[0] += lds[t];
-    }
-    double v = h[0];
-#pragma unroll
-    for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w, 64);
-    return v;
-}
-
-// One record: mass and the force on each body, each summed in an order fixed by
-// the partials alone, so that neither the block size of the launch that runs it
-// nor the way steps are split over calls changes a record by one bit. Block
-// `part` of N_LEAD sums its fixed slice of every partial list (FIN_LANES virtual
-// lanes, then their binary tree, serial_tree) into its stage row; the last
-// block to arrive adds the N_LEAD rows in block order.
-__device__ __forceinline__ void finalize3(const Fin3Args& f, int buf, int part, double* lds, int* flag)
-{
+    static_assert(FIN_LANES == 256, "four virtual lanes per thread");
     const double* pm = f.mass_part + buf * f.mass_stride;
     const double* sf = f.slot_force + buf * f.slot_stride;
-    const int row_len = 1 + 3 * f.max_bodies;
-    double* row = f.stage + (int64_t)part * row_len;
-    const int bd = (int)blockDim.x, t = (int)threadIdx.x, nh = FIN_LANES / bd;
-    const int m0 = (int)((int64_t)f.n_mass * part / N_LEAD), m1 = (int)((int64_t)f.n_mass * (part + 1) / N_LEAD);
-    {
-        double h[SERIAL_H];
-#pragma unroll
-        for (int k = 0; k < SERIAL_H; ++k) h[k] = k < nh ? lane_sum(pm + m0, m1 - m0, t + k * bd) : 0.0;
-        const double m = serial_tree(h, lds);
-        if (t == 0) row[0] = m;
-    }
-    for (int b = 0; b < f.n_bodies; ++b) {   // one pass over the slice serves three components
-        const int s0 = f.body_slot_ptr[b], n = f.body_slot_ptr[b + 1] - s0;
-        const int a0 = s0 + (int)((int64_t)n * part / N_LEAD), a1 = s0 + (int)((int64_t)n * (part + 1) / N_LEAD);
-        double h[3][SERIAL_H];
-#pragma unroll
-        for (int k = 0; k < SERIAL_H; ++k) {
-            double y0 = 0.0, y1 = 0.0, y2 = 0.0;
-            if (k < nh)
-                for (int kk = a0 + t + k * bd; kk < a1; kk += FIN_LANES) {
+    const int l = (int)(threadIdx.x & 63);
+    const int m0 = (int)((int64_t)f.n_mass * part / N_SLICES), m1 = (int)((int64_t)f.n_mass * (part + 1) / N_SLICES);
+    for (int b = -1; b < f.n_bodies; ++b) {   // -1: the mass
+        int a0 = 0, a1 = 0;
+        if (b >= 0) {
+            const int s0 = f.body_slot_ptr[b], n = f.body_slot_ptr[b + 1] - s0;
+            a0 = s0 + (int)((int64_t)n * part / N_SLICES);
+            a1 = s0 + (int)((int64_t)n * (part + 1) / N_SLICES);
+        }
+        double v[3] = {0.0, 0.0, 0.0}, pair[3] = {0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const int lane = l + 64 * ((i >> 1) + 2 * (i & 1));
+            double y[3] = {0.0, 0.0, 0.0};
+            if (b < 0) {
+                y[0] = lane_sum(pm + m0, m1 - m0, lane);
+            } else {
+                for (int kk = a0 + lane; kk < a1; kk += FIN_LANES) {
                     const double* p = sf + 3 * f.body_slots[kk];
-                    y0 += p[0];
-                    y1 += p[1];
-                    y2 += p[2];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) y[c] += p[c];
                 }
-            h[0][k] = y0;
-            h[1][k] = y1;
-            h[2][k] = y2;
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                pair[c] = (i & 1) ? pair[c] + y[c] : y[c];
+                if (i & 1) v[c] = i == 1 ? pair[c] : v[c] + pair[c];
+            }
         }
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const double X = serial_tree(h[c], lds);
-            if (t == 0) row[1 + 3 * b + c] = X;
+        for (int w = 32; w > 0; w >>= 1)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[c] += __shfl_down(v[c], w, 64);
+        if (l == 0) {
+            if (b < 0) {
+                row[0] = v[0];
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) row[1 + 3 * b + c] = v[c];
+            }
         }
     }
-    __threadfence();   // publish the row before counting in
+}
+
+// One block adds a stage buffer's rows in slice order into ring slot r, a column
+// per thread (its rows are fetched at once, then added in order).
+__device__ __forceinline__ void add_rows(const Fin3Args& f, const double* stage, int64_t r)
+{
+    const int row_len = 1 + 3 * f.max_bodies;
+    for (int col = (int)threadIdx.x; col < 1 + 3 * f.n_bodies; col += (int)blockDim.x) {
+        double y[N_SLICES];
+#pragma unroll
+        for (int p = 0; p < N_SLICES; ++p) y[p] = stage[(int64_t)p * row_len + col];
+        double x = 0.0;
+#pragma unroll
+        for (int p = 0; p < N_SLICES; ++p) x += y[p];
+        if (col == 0) f.ring_mass[r] = f.mass_offset + x;
+        else f.ring_force[(r * f.max_bodies + (col - 1) / 3) * 3 + (col - 1) % 3] = x;
+    }
+}
+
+// Leading blocks of a step launch. The record of the previous step: wavefront w of
+// block blk sums slice blk * waves + w. The one before it: its rows are added.
+// Spreading the two stages over two launches needs no fence or counter inside a
+// launch; with one block per batch member doing all slices in turn, the sums
+// outlasted the step of small members (5 FP16 domains of 1.5 M nodes in all in
+// 64-thread blocks: 121 us a step).
+__device__ __forceinline__ void lead_slices(const Fin3Args& f, int buf, int stage, int blk)
+{
+    const int part = blk * (int)(blockDim.x >> 6) + (int)(threadIdx.x >> 6);
+    if (part < N_SLICES) slice_sums(f, buf, part, f.stage[stage] + (int64_t)part * (1 + 3 * f.max_bodies));
+}
+
+__device__ __forceinline__ void lead_add(const Fin3Args& f, int stage)
+{
+    const int64_t count = *f.rec_count;
+    add_rows(f, f.stage[stage], count % f.capacity);
+    __syncthreads();   // every thread has read the count
+    if (threadIdx.x == 0) *f.rec_count = count + 1;
+}
+
+// What a run leaves to sum (launch_finalize3): block blk of
+// N_SLICES / FIN_BLOCK_WAVES. The last block to arrive sees every row and adds
+// both records.
+__device__ __forceinline__ void finalize_run(const Fin3Args& f, int buf, int stage, int add_stage, int blk, int* flag)
+{
+    if (buf < 0) {   // only rows to add
+        if (blk == 0 && add_stage >= 0) lead_add(f, add_stage);
+        return;
+    }
+    lead_slices(f, buf, stage, blk);
+    __threadfence();   // publish the rows before counting in
+    __syncthreads();
     if (threadIdx.x == 0)
-        *flag = atomicAdd(reinterpret_cast<unsigned long long*>(f.arrivals), 1ull) == (unsigned long long)(N_LEAD - 1);
+        *flag = atomicAdd(reinterpret_cast<unsigned long long*>(f.arrivals), 1ull) ==
+                (unsigned long long)(N_SLICES / FIN_BLOCK_WAVES - 1);
     __syncthreads();
     if (!*flag) return;
     __threadfence();   // the other blocks' rows are visible from here on
-    // each column of the N_LEAD rows fetched at once into lds, then added in
-    // row order by one thread
-    int64_t r = 0;
-    if (threadIdx.x == 0) r = *f.rec_count % f.capacity;
-    double mass = 0.0;
-    for (int col = 0; col < 1 + 3 * f.n_bodies; ++col) {
-        __syncthreads();   // lds free from the previous column
-        if ((int)threadIdx.x < N_LEAD) lds[threadIdx.x] = f.stage[(int64_t)threadIdx.x * row_len + col];
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double x = 0.0;
-            for (int p = 0; p < N_LEAD; ++p) x += lds[p];
-            if (col == 0) mass = x;
-            else f.ring_force[(r * f.max_bodies + (col - 1) / 3) * 3 + (col - 1) % 3] = x;
-        }
-    }
+    int64_t count = *f.rec_count;
+    if (add_stage >= 0) add_rows(f, f.stage[add_stage], count++ % f.capacity);
+    add_rows(f, f.stage[stage], count % f.capacity);
+    __syncthreads();   // every thread has read the count
     if (threadIdx.x == 0) {
-        f.ring_mass[r] = f.mass_offset + mass;
-        *f.rec_count += 1;
+        *f.rec_count = count + 1;
         *f.arrivals = 0;
     }
 }
 
-// The same record by one block: the N_LEAD slice sums of finalize3 formed in
-// turn, each with the same virtual lanes and tree, and added in slice order as
-// its last block adds the stage rows, so the result is bitwise the same; no
-// stage rows, fences or arrival counter. For small domains, where the partial
-// lists are short. One pass over a body's slots serves its three components.
-__device__ __forceinline__ void finalize3_serial(const Fin3Args& f, int buf, double* lds)
-{
-    const double* pm = f.mass_part + buf * f.mass_stride;
-    const double* sf = f.slot_force + buf * f.slot_stride;
-    const int bd = (int)blockDim.x, t = (int)threadIdx.x, nh = FIN_LANES / bd;
-    int64_t r = 0;
-    if (t == 0) r = *f.rec_count % f.capacity;
-    double mass = 0.0;
-    for (int part = 0; part < N_LEAD; ++part) {
-        const int m0 = (int)((int64_t)f.n_mass * part / N_LEAD), m1 = (int)((int64_t)f.n_mass * (part + 1) / N_LEAD);
-        double h[SERIAL_H];
-#pragma unroll
-        for (int k = 0; k < SERIAL_H; ++k) h[k] = k < nh ? lane_sum(pm + m0, m1 - m0, t + k * bd) : 0.0;
-        mass += serial_tree(h, lds);
-    }
-    for (int b = 0; b < f.n_bodies; ++b) {
-        const int s0 = f.body_slot_ptr[b], n = f.body_slot_ptr[b + 1] - s0;
-        double x[3] = {0.0, 0.0, 0.0};
-        for (int part = 0; part < N_LEAD; ++part) {
-            const int a0 = s0 + (int)((int64_t)n * part / N_LEAD), a1 = s0 + (int)((int64_t)n * (part + 1) / N_LEAD);
-            double h[3][SERIAL_H];
-#pragma unroll
-            for (int k = 0; k < SERIAL_H; ++k) {
-                double y0 = 0.0, y1 = 0.0, y2 = 0.0;
-                if (k < nh)
-                    for (int kk = a0 + t + k * bd; kk < a1; kk += FIN_LANES) {
-                        const double* p = sf + 3 * f.body_slots[kk];
-                        y0 += p[0];
-                        y1 += p[1];
-                        y2 += p[2];
-                    }
-                h[0][k] = y0;
-                h[1][k] = y1;
-                h[2][k] = y2;
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) x[c] += serial_tree(h[c], lds);
-        }
-        if (t == 0)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) f.ring_force[(r * f.max_bodies + b) * 3 + c] = x[c];
-    }
-    if (t == 0) {
-        f.ring_mass[r] = f.mass_offset + mass;
-        *f.rec_count += 1;
-    }
-}
-
-// A step launch: when the previous step recorded (fin_buf >= 0), N_LEAD leading
-// blocks sum that record while the other blocks stream their tiles.
+// A step launch, behind the leading blocks that sum earlier records.
 template <typename S, int V, bool RECORD, bool FIELDS>
 __global__ void __launch_bounds__(256)
 k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith<S>::R> a)
 {
-    __shared__ double lds[FIN_LANES];   // the record sums; per-wavefront sums of block_sum
-    const int lead = a.fin_buf >= 0 ? N_LEAD : 0;
+    __shared__ double lds[4];   // per-wavefront sums of block_sum
+    const int n_fin = a.fin_buf >= 0 ? slice_blocks(1, a.block) : 0;
+    const int lead = n_fin + (a.add_stage >= 0 ? N_XCD : 0);
     if ((int)blockIdx.x < lead) {
-        __shared__ int last;
-        finalize3(a.fin, a.fin_buf, (int)blockIdx.x, lds, &last);
+        if ((int)blockIdx.x < n_fin) lead_slices(a.fin, a.fin_buf, a.fin_stage, (int)blockIdx.x);
+        else if ((int)blockIdx.x == n_fin) lead_add(a.fin, a.add_stage);
         return;
     }
     const int t = xcd_tile(a.tiles_per_xcd, a.band_log2, lead);
@@ -556,19 +524,25 @@ k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith
 
 // Many domains in one launch: block -> (member, tile) through the tile map; each
 // member's arguments and lattices live in device memory. The members step in
-// lockstep: one step kind, record flag and partial buffer for all; one leading
-// block per member sums that member's previous record (finalize3_serial).
+// lockstep: one step kind, record flag and partial buffer for all; leading
+// blocks sum the members' earlier records.
 template <typename S, int V, bool RECORD, bool FIELDS>
 __global__ void __launch_bounds__(256) k_step3_batch(Batch3Launch b)
 {
     using R = typename Arith<S>::R;
-    __shared__ double lds[FIN_LANES];
+    __shared__ double lds[4];
     const Member3<R>* m = static_cast<const Member3<R>*>(b.members);
-    if ((int)blockIdx.x < b.n_fin) {
-        if ((int)blockIdx.x < b.n_members) finalize3_serial(m[blockIdx.x].a.fin, b.fin_buf, lds);
+    if ((int)blockIdx.x < b.n_fin + b.n_add) {
+        const int blk = (int)blockIdx.x;
+        if (blk < b.n_fin) {
+            const int per = N_SLICES / (int)(blockDim.x >> 6), d = blk / per;
+            if (d < b.n_members) lead_slices(m[d].a.fin, b.fin_buf, b.fin_stage, blk - d * per);
+        } else if (blk - b.n_fin < b.n_members) {
+            lead_add(m[blk - b.n_fin].a.fin, b.add_stage);
+        }
         return;
     }
-    const int g = xcd_tile(b.tiles_per_xcd, b.band_log2, b.n_fin);
+    const int g = xcd_tile(b.tiles_per_xcd, b.band_log2, b.n_fin + b.n_add);
     if (g >= b.total_tiles) return;   // whole block
 #if defined(__HIP_DEVICE_COMPILE__)
     // the tile map and the members do not change during a launch: read through
@@ -590,21 +564,23 @@ __global__ void __launch_bounds__(256) k_step3_batch(Batch3Launch b)
     step3_body<S, V, RECORD, FIELDS>(src, dst, md.a, t, b.part_buf, lds);
 }
 
-// The last record of an lbvp3_batch_step call: one block per member.
+// The last records of an lbvp3_batch_step call.
 template <typename R>
-__global__ void __launch_bounds__(FIN_THREADS) k_finalize3_members(Batch3Launch b)
+__global__ void __launch_bounds__(64 * FIN_BLOCK_WAVES) k_finalize3_members(Batch3Launch b)
 {
-    __shared__ double lds[FIN_LANES];
+    __shared__ int last;
     const Member3<R>* m = static_cast<const Member3<R>*>(b.members);
-    finalize3_serial(m[blockIdx.x].a.fin, b.fin_buf, lds);
+    constexpr int per = N_SLICES / FIN_BLOCK_WAVES;
+    const int d = (int)blockIdx.x / per;
+    finalize_run(m[d].a.fin, b.fin_buf, b.fin_stage, b.add_stage, (int)blockIdx.x - d * per, &last);
 }
 
-// The last record of an lbvp3_step call, summed on its own (N_LEAD blocks).
-__global__ void __launch_bounds__(FIN_THREADS) k_finalize3(Fin3Args f, int32_t buf)
+// The last records of an lbvp3_step call.
+__global__ void __launch_bounds__(64 * FIN_BLOCK_WAVES) k_finalize3(Fin3Args f, int32_t buf, int32_t stage,
+                                                                    int32_t add_stage)
 {
-    __shared__ double lds[FIN_LANES];
     __shared__ int last;
-    finalize3(f, buf, (int)blockIdx.x, lds, &last);
+    finalize_run(f, buf, stage, add_stage, (int)blockIdx.x, &last);
 }
 
 // ------------------------------------------------------------ conversions --
@@ -683,7 +659,8 @@ hipError_t step_v(bool record, bool fields, const S* in, S* out, const Step3Args
                   hipStream_t s)
 {
     using R = typename Arith<S>::R;
-    const dim3 grid((unsigned)(a.tiles_per_xcd * N_XCD + (a.fin_buf >= 0 ? N_LEAD : 0))), block((unsigned)a.block);
+    const int lead = (a.fin_buf >= 0 ? slice_blocks(1, a.block) : 0) + (a.add_stage >= 0 ? N_XCD : 0);
+    const dim3 grid((unsigned)(a.tiles_per_xcd * N_XCD + lead)), block((unsigned)a.block);
     const size_t lds = record ? 3 * (size_t)V * (size_t)a.block * sizeof(R) : 0;
     if (record) {
         if (fields) hipLaunchKernelGGL((k_step3<S, V, true, true>), grid, block, lds, s, in, out, a);
@@ -720,7 +697,7 @@ template <typename S, int V>
 hipError_t batch_v(bool record, bool fields, const Batch3Launch& b, int32_t block, hipStream_t s)
 {
     using R = typename Arith<S>::R;
-    const dim3 grid((unsigned)(b.tiles_per_xcd * N_XCD + b.n_fin)), blk((unsigned)block);
+    const dim3 grid((unsigned)(b.tiles_per_xcd * N_XCD + b.n_fin + b.n_add)), blk((unsigned)block);
     const size_t lds = record ? 3 * (size_t)V * (size_t)block * sizeof(R) : 0;
     if (record) {
         if (fields) hipLaunchKernelGGL((k_step3_batch<S, V, true, true>), grid, blk, lds, s, b);
@@ -790,14 +767,16 @@ hipError_t launch_step3_batch(int32_t storage, int32_t vec, int32_t block, bool 
 
 hipError_t launch_finalize3_members(int32_t storage, const Batch3Launch& b, hipStream_t s)
 {
-    if (storage == LBVP_F64) hipLaunchKernelGGL(k_finalize3_members<double>, dim3(b.n_members), dim3(FIN_THREADS), 0, s, b);
-    else hipLaunchKernelGGL(k_finalize3_members<float>, dim3(b.n_members), dim3(FIN_THREADS), 0, s, b);
+    const dim3 grid((unsigned)(b.n_members * (N_SLICES / FIN_BLOCK_WAVES))), block(64 * FIN_BLOCK_WAVES);
+    if (storage == LBVP_F64) hipLaunchKernelGGL(k_finalize3_members<double>, grid, block, 0, s, b);
+    else hipLaunchKernelGGL(k_finalize3_members<float>, grid, block, 0, s, b);
     return hipGetLastError();
 }
 
-hipError_t launch_finalize3(const Fin3Args& a, int32_t buf, hipStream_t s)
+hipError_t launch_finalize3(const Fin3Args& a, int32_t buf, int32_t stage, int32_t add_stage, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize3, dim3(N_LEAD), dim3(FIN_THREADS), 0, s, a, buf);
+    hipLaunchKernelGGL(k_finalize3, dim3(N_SLICES / FIN_BLOCK_WAVES), dim3(64 * FIN_BLOCK_WAVES), 0, s, a, buf, stage,
+                       add_stage);
     return hipGetLastError();
 }
 

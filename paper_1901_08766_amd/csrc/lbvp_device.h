@@ -364,20 +364,6 @@ __device__ __forceinline__ double lane_sum(const double* x, int n, int v)
     return ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
 }
 
-// Sum of the FIN_LANES values in s (LDS), pairwise with halving spans; every
-// thread of the block must call it and gets the sum.
-__device__ __forceinline__ double tree_sum(double* s)
-{
-    for (int w = FIN_LANES / 2; w > 0; w >>= 1) {
-        __syncthreads();
-        for (int v = (int)threadIdx.x; v < w; v += (int)blockDim.x) s[v] += s[v + w];
-    }
-    __syncthreads();
-    const double r = s[0];
-    __syncthreads();   // s is reused by the next sum
-    return r;
-}
-
 // Block -> tile order. Workgroups are dealt to the 8 XCDs round-robin by block
 // id, and each XCD has its own L2. Counting blocks from first_block:
 //  - band_log2 < 0: block b takes tile (b % 8) * per_xcd + b / 8, so each XCD
