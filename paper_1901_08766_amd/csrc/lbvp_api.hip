@@ -55,6 +55,7 @@ struct Layout {
     int64_t slot_cap = 0, capacity = 0;
     int32_t max_bodies = 0;
     int64_t stage_rows = 0;
+    size_t stage_bytes = 0;
     size_t lat[2] = {0, 0}, mask = 0, bodies = 0, fields = 0, mass_part = 0, slot_force = 0,
            tile_slot_ptr = 0, slot_body = 0, body_slot_ptr = 0, body_slots = 0, ring_force = 0,
            ring_mass = 0, rec_count = 0, stage = 0, ghost_w = 0, ghost_e = 0, pose = 0, pose_base = 0, total = 0;
@@ -224,6 +225,7 @@ Layout make_layout(const lbvp_params* p)
     L.ghost_w = take(3 * (size_t)p->ny * es);
     L.ghost_e = take(3 * (size_t)p->ny * es);
     L.stage = take(stage_bytes);
+    L.stage_bytes = stage_bytes;
     L.pose = take((p->flags & LBVP_MOVING_BODIES) ? (size_t)POSE_ROWS * MAX_MOVING * POSE_STRIDE * sizeof(double) : 0);
     L.pose_base = take((p->flags & LBVP_MOVING_BODIES) ? sizeof(int64_t) : 0);
     L.total = o;
@@ -296,8 +298,8 @@ struct lbvp_ctx {
     int cur = 0;                // lattice holding the current post-collision state
     int64_t step = 0;
     int64_t rec_head = 0, rec_tail = 0;
-    bool pending = false;       // a recorded step whose sums are not yet in the ring
-    int32_t pending_buf = 0;
+    int32_t pending = 0;        // records of the last launch whose sums are not yet in the ring ...
+    int32_t pending_buf = 0;    // ... and the partial buffer of the first of them
     bool fields_valid = false;
     int32_t n_bodies = 0;
     double tau_minus = 0.0;
@@ -406,11 +408,12 @@ void fill_step_args(lbvp_ctx* c, StepArgs<R>& a)
     a.bodies = c->at<R>(L.bodies);
     a.tile_slot_ptr = c->at<int32_t>(L.tile_slot_ptr);
     a.slot_body = c->at<int32_t>(L.slot_body);
-    a.slot_force = c->at<double>(L.slot_force);
-    a.mass_part = c->at<double>(L.mass_part);
+    a.slot_force = const_cast<double*>(c->fin.slot_force);
+    a.mass_part = const_cast<double*>(c->fin.mass_part);
     a.fields = c->at<R>(L.fields);
     a.part_buf = 0;
-    a.fin_buf = -1;
+    a.fin_buf = 0;
+    a.fin_n = 0;
     a.ghost_w = c->at<char>(L.ghost_w);
     a.ghost_e = c->at<char>(L.ghost_e);
     a.fin = c->fin;
@@ -455,6 +458,33 @@ std::vector<char> body_table_bytes(const lbvp_body* bodies, int32_t n, int32_t m
     std::vector<char> out(t.size() * sizeof(R));
     std::memcpy(out.data(), t.data(), out.size());
     return out;
+}
+
+// Where the record partials of the current tiling live and how many buffers they
+// have: four if they fit the tables' areas (vector launches need a fraction of
+// them, which are sized for the finest tiling) or the staging area (which only
+// conversions between runs use), else two.
+void place_partials(lbvp_ctx* c, size_t n_slots)
+{
+    const Layout& L = c->L;
+    const int64_t n_mass = (int64_t)c->launch.n_tiles * (c->launch.block / 64), n_force = 2 * (int64_t)n_slots;
+    c->fin.mass_part = c->at<double>(L.mass_part);
+    c->fin.slot_force = c->at<double>(L.slot_force);
+    c->fin.mass_stride = L.max_waves;
+    c->fin.slot_stride = L.slot_cap * 2;
+    c->fin.n_buf = 2;
+    if (c->moving()) return;   // their slots change between runs
+    if (4 * n_mass <= 2 * (int64_t)L.max_waves && 4 * n_force <= 4 * L.slot_cap) {
+        c->fin.mass_stride = n_mass;
+        c->fin.slot_stride = n_force;
+        c->fin.n_buf = 4;
+    } else if ((size_t)(4 * (n_mass + n_force)) * sizeof(double) <= L.stage_bytes) {
+        c->fin.mass_part = c->at<double>(L.stage);
+        c->fin.slot_force = c->at<double>(L.stage) + 4 * n_mass;
+        c->fin.mass_stride = n_mass;
+        c->fin.slot_stride = n_force;
+        c->fin.n_buf = 4;
+    }
 }
 
 // The (tile, body) reduction tables for the current tiling and mask: a slot per
@@ -560,6 +590,10 @@ lbvp_status build_tile_tables(lbvp_ctx* c)
     LBVP_HIP(c, hipMemcpyAsync(c->at<int32_t>(L.body_slot_ptr), body_ptr.data(), body_ptr.size() * 4,
                                hipMemcpyHostToDevice, s));
     LBVP_HIP(c, hipStreamSynchronize(s));  // the host tables above go out of scope
+    place_partials(c, slot_body.size());
+    c->a64.fin = c->a32.fin = c->fin;
+    c->a64.slot_force = c->a32.slot_force = const_cast<double*>(c->fin.slot_force);
+    c->a64.mass_part = c->a32.mass_part = const_cast<double*>(c->fin.mass_part);
     return LBVP_OK;
 }
 
@@ -614,7 +648,8 @@ hipError_t refresh_aa_ghosts(lbvp_ctx* c)
 struct CtxClock {
     int cur;
     int64_t step, rec_head;
-    bool pending, fields_valid;
+    int32_t pending;
+    bool fields_valid;
     int32_t pending_buf;
 };
 
@@ -658,52 +693,97 @@ lbvp_status pose_window(lbvp_ctx* c, int64_t next, int64_t n)
     return st;
 }
 
-// n steps from the current state, one launch each, then the standalone sum of
-// the last record. With launch == false only the bookkeeping advances (the
-// same launches were replayed from a graph). Moving bodies: the pose table
-// must hold the run's time levels (pose_window).
+// Whether the context's coming steps run two to a launch (k_march): FP64 or FP32
+// vector launches of the pull layout with a fixed mask and no slab cut, tiles that
+// are single rows, room for the partials of four records (place_partials), and
+// more rows of tiles than the chip holds wavefronts of k_march (MARCH_WAVES), so
+// that its chunks have two rows or more. Measured, two steps per launch against
+// one, us per step, recording every step: FP32 8192 x 4096 252 against 385, 3072 x
+// 1536 46.0 against 60.4, 2048 x 1024 24.2 against 29.2; FP64 488 against 782, 78
+// against 115, and 1024 x 1024 25.2 against 28.7. Below the line there is too
+// little to fill the chip: FP32 1024 x 512 12.9 against 9.4. One node per thread
+// loses everywhere (1024 x 512 11.5 against 9.1), and 2-byte storage is bound by its
+// conversions and arithmetic: FP16 8192 x 4096 195 against 203, but BF16 2305 x 1153
+// 30 against 23. An offset within a row has to fit 31 bits.
+bool can_march(const lbvp_ctx* c)
+{
+    const Launch& l = c->launch;
+    return (c->p.storage == LBVP_F64 || c->p.storage == LBVP_F32) && l.vec > 1 && !c->aa() && !c->moving() &&
+           c->p.bc_west != LBVP_BC_NEIGHBOR && c->p.bc_east != LBVP_BC_NEIGHBOR && l.tile_rows == 1 &&
+           c->fin.n_buf == 4 && c->L.lstride * (int64_t)c->esize() < (int64_t(1) << 30) &&
+           (int64_t)l.n_tiles * (l.block / 64) > MARCH_WAVES;
+}
+
+// The chunks of a two-step launch: as few rows as still let the chip hold all
+// workgroups at once, up to 6, for a chunk of H rows does H + 2 rows of the first
+// step. Above 6 the rows a workgroup takes one after the other cost more than the
+// repeated ones: FP32 8192 x 4096 with H = 4, 6, 8, 16, 32: 257, 252, 254, 276,
+// 309 us per step, FP64 513, 492, 488, 506, -.
+MarchArgs march_args(const lbvp_ctx* c)
+{
+    const Launch& l = c->launch;
+    const int64_t waves = (int64_t)l.n_tiles * (l.block / 64);
+    MarchArgs m{};
+    m.rows = (int32_t)std::min<int64_t>((waves + MARCH_WAVES - 1) / MARCH_WAVES, MARCH_ROWS);
+    m.n_chunks = (c->p.ny + m.rows - 1) / m.rows;
+    m.per_xcd = (m.n_chunks * l.tiles_x + N_XCD - 1) / N_XCD;
+    return m;
+}
+
+// n steps from the current state, one launch each or one per pair, then the
+// standalone sum of the last launch's records. With launch == false only the
+// bookkeeping advances (the same launches were replayed from a graph). Moving
+// bodies: the pose table must hold the run's time levels (pose_window).
 lbvp_status enqueue_steps(lbvp_ctx* c, int64_t n_steps, bool keep_last, bool launch)
 {
     const int64_t fe = c->p.force_every;
     c->a64.fin = c->fin;
     c->a32.fin = c->fin;
-    for (int64_t k = 0; k < n_steps; ++k) {
-        const int64_t next = c->step + 1;
-        const bool record = fe > 0 && next % fe == 0;
-        const bool keep = keep_last && k == n_steps - 1;
-        const int32_t part_buf = (int32_t)(c->rec_head & 1);
+    const bool march = can_march(c);
+    MarchArgs m{};
+    if (march) m = march_args(c);
+    const void* args = c->is_f64() ? (const void*)&c->a64 : (const void*)&c->a32;
+    for (int64_t k = 0; k < n_steps;) {
+        // the step that keeps the fields runs alone
+        const int64_t n = march && n_steps - k >= (keep_last ? 3 : 2) ? 2 : 1;
+        const bool keep = keep_last && k + n == n_steps;
+        const int32_t part_buf = (int32_t)(c->rec_head & (c->fin.n_buf - 1));
+        const bool rec0 = fe > 0 && (c->step + 1) % fe == 0, rec1 = n == 2 && fe > 0 && (c->step + 2) % fe == 0;
         if (launch) {
-            const int32_t fin_buf = c->pending ? c->pending_buf : -1;
             c->a64.part_buf = c->a32.part_buf = part_buf;
-            c->a64.fin_buf = c->a32.fin_buf = fin_buf;
-            const void* args = c->is_f64() ? (const void*)&c->a64 : (const void*)&c->a32;
+            c->a64.fin_buf = c->a32.fin_buf = c->pending_buf;
+            c->a64.fin_n = c->a32.fin_n = c->pending;
+            char* src = c->at<char>(c->L.lat[c->cur]);
+            char* dst = c->at<char>(c->L.lat[c->cur ^ 1]);
             const int32_t mode = !c->aa() ? MODE_PULL : (c->step % 2 == 0 ? MODE_AA_PUSH : MODE_AA_LOCAL);
             hipError_t e;
-            if (c->moving()) {   // row *pose_base + k: the poses at the time level this step computes
+            if (n == 2) {
+                m.rec = (rec0 ? 1 : 0) | (rec1 ? 2 : 0);
+                e = launch_march(c->p.storage, src, dst, args, m, c->stream);
+            } else if (c->moving()) {   // row *pose_base + k: the poses at the time level this step computes
                 c->a64.pose_k = c->a32.pose_k = (int32_t)k;
-                e = launch_step_moving(c->p.storage, mode, record, keep, c->at<char>(c->L.lat[c->cur]),
-                                       c->at<char>(c->L.lat[c->cur ^ 1]), args, c->stream);
+                e = launch_step_moving(c->p.storage, mode, rec0, keep, src, dst, args, c->stream);
             } else {
-                e = launch_step(c->p.storage, mode, record, keep, c->at<char>(c->L.lat[c->cur]),
-                                c->at<char>(c->L.lat[c->cur ^ 1]), args, c->stream);
+                e = launch_step(c->p.storage, mode, rec0, keep, src, dst, args, c->stream);
             }
             if (e != hipSuccess) return c->hip_fail(e, "step kernel launch");
         }
-        c->pending = record;
-        if (record) {
+        c->pending = (rec0 ? 1 : 0) + (rec1 ? 1 : 0);
+        if (c->pending) {
             c->pending_buf = part_buf;
-            c->rec_head += 1;
+            c->rec_head += c->pending;
         }
         if (keep) c->fields_valid = true;
         if (!c->aa()) c->cur ^= 1;
-        c->step = next;
+        c->step += n;
+        k += n;
     }
-    if (c->pending) {  // the last record of the run is summed on its own
+    if (c->pending) {  // the last records of the run are summed on their own
         if (launch) {
-            hipError_t e = launch_finalize(c->fin, c->pending_buf, c->stream);
+            hipError_t e = launch_finalize(c->fin, c->pending_buf, c->pending, c->stream);
             if (e != hipSuccess) return c->hip_fail(e, "finalize kernel launch");
         }
-        c->pending = false;
+        c->pending = 0;
     }
     if (launch && c->moving() && n_steps > 0) {   // the next run's first pose row
         hipError_t e = launch_pose_advance(c->at<int64_t>(c->L.pose_base), n_steps, c->stream);
@@ -862,7 +942,7 @@ void batch_fill_args(lbvp_batch* b)
             a.lat1 = c->at<char>(c->L.lat[1]);
             a.cur = c->cur;
             a.part_buf = 0;
-            a.fin_buf = -1;
+            a.fin_n = 0;
             std::memcpy(dst, &a, sizeof(a));
         } else {
             StepArgs<float> a = c->a32;
@@ -871,7 +951,7 @@ void batch_fill_args(lbvp_batch* b)
             a.lat1 = c->at<char>(c->L.lat[1]);
             a.cur = c->cur;
             a.part_buf = 0;
-            a.fin_buf = -1;
+            a.fin_n = 0;
             std::memcpy(dst, &a, sizeof(a));
         }
         std::memcpy(b->image.data() + b->off_fins + d * sizeof(FinalizeArgs), &c->fin, sizeof(FinalizeArgs));
@@ -1354,7 +1434,7 @@ lbvp_status lbvp_init_equilibrium(lbvp_ctx* c, const double* rho, const double* 
     c->step = 0;
     c->pose_first = -1;   // the step count starts again: so do the poses
     c->rec_head = c->rec_tail = 0;
-    c->pending = false;
+    c->pending = 0;
     c->fields_valid = true;
     return LBVP_OK;
 }
@@ -1396,7 +1476,7 @@ lbvp_status lbvp_step(lbvp_ctx* c, int64_t n_steps, uint32_t flags)
         key.cur = c->cur;
         key.par = c->aa() ? (int32_t)(c->step & 1) : 0;
         key.phase = fe > 0 ? c->step % fe : 0;
-        key.rec = (int32_t)(c->rec_head & 1);
+        key.rec = (int32_t)(c->rec_head & (c->fin.n_buf - 1));
         key.gen = c->gen;
         hipGraphExec_t x = c->graphs.find(key);
         if (x) {
@@ -1578,7 +1658,7 @@ StateHeader state_header(const lbvp_ctx* c)
     h.storage = c->p.storage;
     h.layout = c->p.flags & LBVP_LAYOUT_AA;
     h.n_bodies = c->n_bodies;
-    h.cur = c->cur;
+    h.cur = c->aa() ? 0 : (int32_t)(c->step & 1);   // whichever lattice a launch of two steps left it in
     h.fields_valid = c->fields_valid ? 1 : 0;
     h.step = c->step;
     h.records = c->rec_head;
@@ -1666,7 +1746,7 @@ lbvp_status lbvp_load_state(lbvp_ctx* c, const void* buf, size_t size)
     c->step = h.step;
     c->pose_first = -1;
     c->rec_head = c->rec_tail = h.records;
-    c->pending = false;
+    c->pending = 0;
     c->fields_valid = h.fields_valid != 0;
     c->gen += 1;
     return LBVP_OK;

@@ -38,17 +38,19 @@ enum Storage : int32_t { ST_F64 = 0, ST_F32 = 1, ST_F16 = 2, ST_BF16 = 3 };
 
 // Sums one force record: the per-wavefront mass partials and the (tile, body)
 // force partials of partial buffer `buf`, in a fixed order, into ring slot
-// rec_count % capacity. The partials are double-buffered so that the record of
-// step k can be summed while step k + 1 writes its own.
+// rec_count % capacity. The partials have n_buf buffers, taken in turn, so that
+// the records of one launch can be summed while the next writes its own: two
+// for launches of one step, four where launches of two steps run.
 struct FinalizeArgs {
     int32_t n_bodies, max_bodies, n_mass;   // n_mass: wavefronts of a launch
     int64_t capacity;
     double mass_offset;             // rho0 * nx * ny
     const int32_t* body_slot_ptr;   // [n_bodies + 1]
     const int32_t* body_slots;      // slots of each body in tile order
-    const double* slot_force;       // [2][slot_stride / 2][2]
-    const double* mass_part;        // [2][mass_stride]
+    const double* slot_force;       // [n_buf][slot_stride / 2][2]
+    const double* mass_part;        // [n_buf][mass_stride]
     int64_t slot_stride, mass_stride;
+    int32_t n_buf;                  // a power of two
     double* ring_force;             // [capacity][max_bodies][2]
     double* ring_mass;              // [capacity]
     int64_t* rec_count;             // [FIN_COUNTERS] records written so far, all equal between launches
@@ -63,7 +65,8 @@ struct StepArgs {
     int32_t band_log2;  // block -> tile order (xcd_tile): -1 eighths, else bands of 2^band_log2 tiles
     int32_t west, east;
     int32_t part_buf;   // partial buffer a recording step writes
-    int32_t fin_buf;    // partial buffer whose record a leading block of the launch sums, or -1
+    int32_t fin_buf;    // partial buffer of the first record that leading blocks of the launch sum
+    int32_t fin_n;      // how many records they sum (0: none), in consecutive buffers
     int32_t off32;      // a lattice spans fewer than 2^32 bytes: per-lane offsets fit 32 bits
     int64_t pitch;      // elements per row of one population, of the mask and of a field
     int64_t plane;      // elements between the rows of populations q and q + 1 (= pitch)
@@ -87,8 +90,8 @@ struct StepArgs {
     const R* bodies;    // [(n_bodies + 1)][BODY_STRIDE] (body_table_bytes); row 0 all zero (fluid)
     const int32_t* tile_slot_ptr;   // [n_tiles + 1]
     const int32_t* slot_body;       // [n_slots]
-    double* slot_force;             // [2][n_slots][2]
-    double* mass_part;              // [2][n_tiles * block / 64]
+    double* slot_force;             // as in FinalizeArgs
+    double* mass_part;
     R* fields;                      // [5][plane_f]
     void* ghost_w;                  // AA layout: [3][ny] zero-gradient ghost columns (storage type)
     void* ghost_e;
@@ -108,6 +111,17 @@ struct StepArgs {
     int32_t pose_k;
     const int64_t* pose_base;
     const double* pose;
+};
+
+// A launch of two steps (k_march): the strips are the launch shape's tile
+// columns, cut into chunks of `rows` rows.
+constexpr int MARCH_ROWS = 6;       // most rows of a chunk
+constexpr int MARCH_WAVES = 3072;   // wavefronts of it the chip holds: 1024 SIMDs, 3 each
+struct MarchArgs {
+    int32_t rows, n_chunks;         // rows per chunk, chunks per strip
+    int32_t per_xcd;                // ceil(chunks * strips / 8)
+    int32_t rec;                    // bit 0: the first step records (partial buffer part_buf), bit 1: the
+                                    // second (the buffer after it if the first does, else part_buf)
 };
 
 // A launch over many domains (k_step_batch).
@@ -191,7 +205,15 @@ struct StepLaunch {
                             const BatchLaunch& b, hipStream_t s);
 };
 
+// The two-step launch of one storage type (lbvp_march.h).
+template <typename S>
+struct MarchLaunch {
+    static hipError_t one(const void* src, void* dst, const void* step_args, const MarchArgs& m, hipStream_t s);
+};
+
 // launchers (lbvp_kernels.hip); all return the launch status
+hipError_t launch_march(int32_t storage, const void* src, void* dst, const void* step_args, const MarchArgs& m,
+                        hipStream_t s);
 hipError_t launch_step(int32_t storage, int32_t mode, bool record, bool fields, const void* src, void* dst,
                        const void* step_args, hipStream_t s);
 // the same with the mask moved to the step's time level (one node per thread)
@@ -207,7 +229,8 @@ hipError_t launch_pose_advance_batch(int32_t storage, const void* args, int32_t 
 hipError_t launch_finalize_batch(const FinalizeArgs* fin_dev, int32_t n, int32_t buf, hipStream_t s);
 // leading blocks per domain of a batch of n domains
 int32_t batch_fin_share(int32_t n);
-hipError_t launch_finalize(const FinalizeArgs& a, int32_t buf, hipStream_t s);
+// n records, in partial buffers buf, buf + 1, ...
+hipError_t launch_finalize(const FinalizeArgs& a, int32_t buf, int32_t n, hipStream_t s);
 hipError_t launch_init(int32_t storage, void* lat, void* fields, const ConvArgs& a, hipStream_t s);
 hipError_t launch_decode(int32_t storage, const void* lat, const ConvArgs& a, hipStream_t s);
 hipError_t launch_encode(int32_t storage, void* lat, const ConvArgs& a, hipStream_t s);

@@ -13,11 +13,11 @@
 namespace lbvp {
 namespace {
 
-// The last record of an lbvp_step call, summed on its own.
-__global__ void __launch_bounds__(FIN_THREADS) k_finalize(FinalizeArgs a, int32_t buf)
+// The last records of an lbvp_step call, summed on their own.
+__global__ void __launch_bounds__(FIN_THREADS) k_finalize(FinalizeArgs a, int32_t buf, int32_t n)
 {
     __shared__ double lds[2 * FIN_LANES];
-    finalize_record(a, buf, (int)blockIdx.x, FIN_COUNTERS, lds);
+    finalize_record(a, buf, n, (int)blockIdx.x, FIN_COUNTERS, lds);
 }
 
 // The same for every domain of a batch.
@@ -25,7 +25,7 @@ __global__ void __launch_bounds__(FIN_THREADS) k_finalize_batch(const FinalizeAr
 {
     __shared__ double lds[2 * FIN_LANES];
     const int d = (int)blockIdx.x / share;
-    finalize_record(fins[d], buf, (int)blockIdx.x - d * share, share, lds);
+    finalize_record(fins[d], buf, 1, (int)blockIdx.x - d * share, share, lds);
 }
 
 // Moving bodies: after a run of n steps, the pose table row of the next step.
@@ -227,6 +227,16 @@ hipError_t launch_step_batch(int32_t storage, int32_t vec, int32_t block, int32_
     }
 }
 
+hipError_t launch_march(int32_t storage, const void* src, void* dst, const void* step_args, const MarchArgs& m,
+                        hipStream_t s)
+{
+    switch (storage) {
+    case ST_F64: return MarchLaunch<double>::one(src, dst, step_args, m, s);
+    case ST_F32: return MarchLaunch<float>::one(src, dst, step_args, m, s);
+    default: return hipErrorInvalidValue;   // 2-byte storage runs single steps
+    }
+}
+
 hipError_t launch_pose_advance(int64_t* base, int64_t n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_pose_advance, dim3(1), dim3(1), 0, s, base, n);
@@ -269,9 +279,9 @@ hipError_t launch_aa_ghosts(int32_t storage, const void* lat, const GhostArgs& a
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const FinalizeArgs& a, int32_t buf, hipStream_t s)
+hipError_t launch_finalize(const FinalizeArgs& a, int32_t buf, int32_t n, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_finalize, dim3(FIN_COUNTERS), dim3(FIN_THREADS), 0, s, a, buf);
+    hipLaunchKernelGGL(k_finalize, dim3(FIN_COUNTERS), dim3(FIN_THREADS), 0, s, a, buf, n);
     return hipGetLastError();
 }
 

@@ -313,8 +313,9 @@ __device__ __forceinline__ void record_tree(const double* sx, const double* sy, 
     __syncthreads();   // sx and sy are reused by the next sum
 }
 
-// Share blk of n_blk blocks (n_blk divides FIN_COUNTERS) of one record's sums:
-// the mass and every body are a unit each, dealt out in turn, so that the sums
+// Share blk of n_blk blocks (n_blk divides FIN_COUNTERS) of the sums of n_rec
+// records, in partial buffers buf, buf + 1, ... : a record's mass and every one
+// of its bodies are a unit each, dealt out in turn, so that the sums
 // of a record, each a chain of dependent loads and a tree, run side by side.
 // With one block doing them one after the other, the chain outlasted the step of
 // a small domain: 64 x 64 nodes in FP64 with two bodies took 10.9 us a step.
@@ -323,16 +324,17 @@ __device__ __forceinline__ void record_tree(const double* sx, const double* sy, 
 // record_tree; neither the block size nor n_blk changes a record by one bit.
 // Each share counts the records itself: counters blk, blk + n_blk, ... are its
 // own, so no block waits for another.
-__device__ __forceinline__ void finalize_record(const FinalizeArgs& f, int buf, int blk, int n_blk, double* lds)
+__device__ __forceinline__ void finalize_record(const FinalizeArgs& f, int buf, int n_rec, int blk, int n_blk, double* lds)
 {
-    const double* pm = f.mass_part + buf * f.mass_stride;
-    const double* sf = f.slot_force + buf * f.slot_stride;
     double* sx = lds;
     double* sy = lds + FIN_LANES;
     const int64_t count = f.rec_count[blk];
-    const int64_t r = count % f.capacity;
-    for (int unit = blk; unit <= f.n_bodies; unit += n_blk) {
-        const int b = unit - 1;
+    const int per = f.n_bodies + 1;
+    for (int unit = blk; unit < n_rec * per; unit += n_blk) {
+        const int rec = unit / per, b = unit - rec * per - 1;   // b = -1: the mass
+        const int64_t pb = (buf + rec) & (f.n_buf - 1), r = (count + rec) % f.capacity;
+        const double* pm = f.mass_part + pb * f.mass_stride;
+        const double* sf = f.slot_force + pb * f.slot_stride;
         if (b < 0) {
             for (int v = (int)threadIdx.x; v < FIN_LANES; v += (int)blockDim.x) {
                 sx[v] = lane_sum(pm, f.n_mass, v);
@@ -381,7 +383,7 @@ __device__ __forceinline__ void finalize_record(const FinalizeArgs& f, int buf, 
         }
     }
     if (threadIdx.x == 0)
-        for (int c = blk; c < FIN_COUNTERS; c += n_blk) f.rec_count[c] = count + 1;
+        for (int c = blk; c < FIN_COUNTERS; c += n_blk) f.rec_count[c] = count + n_rec;
 }
 
 }  // namespace

@@ -463,9 +463,9 @@ k_step(const S* __restrict__ src, S* __restrict__ dst, StepArgs<typename Arith<S
 {
     __shared__ double lds[2 * FIN_LANES];   // the record sums, then the per-wavefront sums
     // the first 8 blocks sum the previous step's record (no block waits on them)
-    const int lead = a.fin_buf >= 0 ? N_XCD : 0;
+    const int lead = a.fin_n > 0 ? N_XCD : 0;
     if ((int)blockIdx.x < lead) {
-        finalize_record(a.fin, a.fin_buf, (int)blockIdx.x, N_XCD, lds);
+        finalize_record(a.fin, a.fin_buf, a.fin_n, (int)blockIdx.x, N_XCD, lds);
         return;
     }
     const int t = xcd_tile(a.tiles_per_xcd, a.band_log2, lead);
@@ -478,9 +478,9 @@ template <typename S, int V, int MODE, bool RECORD, bool FIELDS, bool MOVING = f
 __global__ void __launch_bounds__(256) k_step_aa(S* lat, StepArgs<typename Arith<S>::R> a)
 {
     __shared__ double lds[2 * FIN_LANES];
-    const int lead = a.fin_buf >= 0 ? N_XCD : 0;
+    const int lead = a.fin_n > 0 ? N_XCD : 0;
     if ((int)blockIdx.x < lead) {
-        finalize_record(a.fin, a.fin_buf, (int)blockIdx.x, N_XCD, lds);
+        finalize_record(a.fin, a.fin_buf, a.fin_n, (int)blockIdx.x, N_XCD, lds);
         return;
     }
     const int t = xcd_tile(a.tiles_per_xcd, a.band_log2, lead);
@@ -503,7 +503,7 @@ __global__ void __launch_bounds__(256) k_step_batch(BatchLaunch b)
     if ((int)blockIdx.x < b.n_fin) {
         const int d = (int)blockIdx.x / b.fin_share;
         if (d < b.n_domains)
-            finalize_record(args[d].fin, b.fin_buf, (int)blockIdx.x - d * b.fin_share, b.fin_share, lds);
+            finalize_record(args[d].fin, b.fin_buf, 1, (int)blockIdx.x - d * b.fin_share, b.fin_share, lds);
         return;
     }
     const int g = xcd_tile(b.tiles_per_xcd, b.band_log2, b.n_fin);
@@ -542,7 +542,7 @@ template <typename S, int V, bool MOVING = false>
 hipError_t step_v(int mode, bool record, bool fields, const S* in, S* out, const StepArgs<typename Arith<S>::R>& a,
                   hipStream_t s)
 {
-    const dim3 grid((unsigned)(a.tiles_per_xcd * N_XCD + (a.fin_buf >= 0 ? N_XCD : 0))), block((unsigned)a.block);
+    const dim3 grid((unsigned)(a.tiles_per_xcd * N_XCD + (a.fin_n > 0 ? N_XCD : 0))), block((unsigned)a.block);
     const size_t lds = record_lds_bytes<typename Arith<S>::R>(V, a.block);
     if (mode == PULL) {
         if constexpr (sizeof(S) == 2 && V > 1) {
