@@ -260,33 +260,36 @@ constexpr int EXM[3] = {3, 6, 7};   // ex = -1: pulled from column i + 1
 // overwritten by a neighbour in the same kernel.
 enum Mode { PULL = 0, AA_PUSH = 1, AA_LOCAL = 2 };
 
-// Population q pulled from column c (-1 and nx are outside the domain) of plane
-// `plane_q` in the row starting at row_off (row index `row`): the domain sides
-// are resolved here. A NEIGHBOR side (a cut of a slab decomposition) reads the
-// halo column that lbvp_halo_exchange wrote into the current lattice's padding
-// (column nx for the east side, pitch - 1 for the west; a context with a cut has
-// pitch >= nx + 2), so it is one more column choice, like a periodic side, with
-// the same single load. Ghost populations are values of the storage type, like
-// every other population (the AA push step stores the inflow ones in the
+// What row j's boundary column (EAST: the last) pulls from the column outside the
+// domain: populations EXP of a west side, EXM of an east one. A NEIGHBOR side (a
+// cut of a slab decomposition) reads the halo column that lbvp_halo_exchange wrote
+// into the current lattice's padding (column nx for the east side, pitch - 1 for
+// the west; a context with a cut has pitch >= nx + 2), so it is one more column
+// choice, like a periodic side. Ghost populations are values of the storage type,
+// like every other population (the AA push step stores the inflow ones in the
 // lattice), so the inflow equilibrium is rounded to it.
-template <int MODE, typename S, typename R>
-__device__ __forceinline__ R pull_column(const S* src, int q, int plane_q, int64_t row_off, int row, int c,
-                                         const StepArgs<R>& a)
+template <int MODE, bool EAST, typename S, typename R>
+__device__ __forceinline__ void side_column(const S* src, const int64_t (&row_of)[9], int j, int jm, int jp,
+                                            const StepArgs<R>& a, S (&e)[3])
 {
-    if (c < 0) {
-        if (a.west == SIDE_INFLOW_EQ) return dec(enc<S>(a.feq_in[q]));
-        if (MODE == AA_PUSH && a.west == SIDE_OUTFLOW)
-            return dec(static_cast<const S*>(a.ghost_w)[(q == 1 ? 0 : q == 5 ? 1 : 2) * (int64_t)a.ny + row]);
-        // a cut's west halo lives in the row's last padding column
-        c = (a.west == SIDE_PERIODIC) ? a.nx - 1 : (a.west == SIDE_NEIGHBOR ? (int)a.pitch - 1 : 0);
-    } else if (c >= a.nx) {
-        if (a.east == SIDE_INFLOW_EQ) return dec(enc<S>(a.feq_in[q]));
-        if (MODE == AA_PUSH && a.east == SIDE_OUTFLOW)
-            return dec(static_cast<const S*>(a.ghost_e)[(q == 3 ? 0 : q == 6 ? 1 : 2) * (int64_t)a.ny + row]);
-        // a cut's east halo lives in column nx, the first padding column
-        c = (a.east == SIDE_PERIODIC) ? 0 : (a.east == SIDE_NEIGHBOR ? a.nx : a.nx - 1);
+    const int side = EAST ? a.east : a.west;
+    if (side == SIDE_INFLOW_EQ) {
+#pragma unroll
+        for (int m = 0; m < 3; ++m) e[m] = enc<S>(a.feq_in[EAST ? EXM[m] : EXP[m]]);
+    } else if (MODE == AA_PUSH && side == SIDE_OUTFLOW) {
+        const S* ghost = static_cast<const S*>(EAST ? a.ghost_e : a.ghost_w);
+        const int rows[3] = {j, jm, jp};
+#pragma unroll
+        for (int m = 0; m < 3; ++m) e[m] = ghost[m * (int64_t)a.ny + rows[m]];
+    } else {
+        const int c = EAST ? (side == SIDE_PERIODIC ? 0 : (side == SIDE_NEIGHBOR ? a.nx : a.nx - 1))
+                           : (side == SIDE_PERIODIC ? a.nx - 1 : (side == SIDE_NEIGHBOR ? (int)a.pitch - 1 : 0));
+#pragma unroll
+        for (int m = 0; m < 3; ++m) {
+            const int q = EAST ? EXM[m] : EXP[m], pq = MODE == AA_PUSH ? OPP[q] : q;
+            e[m] = src[pq * a.plane + row_of[q] + c];
+        }
     }
-    return dec(src[(int64_t)plane_q * a.plane + row_off + c]);
 }
 
 // ------------------------------------------------------------ the record --

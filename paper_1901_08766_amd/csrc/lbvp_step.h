@@ -76,17 +76,8 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
     if constexpr (MOVING) {      // the poses at this step's time level (a domain with moving bodies)
         if (a.n_moving > 0) bs.pose = a.pose + (*a.pose_base + pose_k) * (int64_t)(MAX_MOVING * POSE_STRIDE);
     }
-    {
-        s0 = a.tile_slot_ptr[t];
-        s1 = a.tile_slot_ptr[t + 1];
-        // the slots list every body with a node in the tile: with none, the
-        // tile's mask is not read at all; with one, its row serves every solid
-        // node of the tile (read here, before any store)
-        if (s1 - s0 == 1) {
-            bs.uniform = true;
-            bs.row = body_row(a.bodies + BODY_STRIDE * a.slot_body[s0]);
-        }
-    }
+    s0 = a.tile_slot_ptr[t];
+    s1 = a.tile_slot_ptr[t + 1];
     const int ty = t / a.tiles_x, tx = t - ty * a.tiles_x;
     const int tpr = a.tile_w / V;                       // threads per tile row (tile_w and V are powers of two)
     const int lr = (int)threadIdx.x >> __builtin_ctz((unsigned)tpr), lc = (int)threadIdx.x & (tpr - 1);
@@ -95,21 +86,6 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
     const int lane = (int)(threadIdx.x & 63);
     const bool act = i0 < a.nx && ty * a.tile_rows + lr < a.ny;   // owns at least one real node
     const int n_own = act ? min(V, a.nx - i0) : 0;
-    if constexpr (MOVING) {
-        if (bs.pose) {   // once per tile: most tiles meet no moving body
-            // only the bodies the tile's slots list can reach it during the
-            // pose window (none for most tiles); of those, the ones whose
-            // radius about this step's centre meets the tile
-            uint32_t listed = 0;
-            for (int s = s0; s < s1; ++s) listed |= 1u << (a.slot_body[s] - 1);
-            if (listed) {
-                const double x0 = (double)(tx * a.tile_w), y0 = (double)(ty * a.tile_rows);
-                bs.near = listed & __builtin_amdgcn_readfirstlane(tile_near_bodies(
-                                       a, bs.pose, x0, x0 + (double)(a.tile_w - 1), y0, y0 + (double)(a.tile_rows - 1)));
-            }
-        }
-    }
-
     const int jm = (j == 0) ? a.ny - 1 : j - 1;     // rows are periodic
     const int jp = (j == a.ny - 1) ? 0 : j + 1;
     const int64_t r0 = (int64_t)j * a.pitch;   // mask and fields
@@ -145,6 +121,31 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
     // lattice, no branch or register clearing is needed, and their results are
     // never stored, summed or shuffled into an owned node.
     const int il = act ? i0 : 0;
+    const int last = a.nx - 1 - i0;      // this thread's index of the domain's last column, if 0 .. V - 1
+    // Everything the step reads is requested before anything is waited for: the
+    // columns next to a thread's own where no lane move or shifted load has them
+    // (at the domain's sides, what stands for the column outside it; left as the
+    // storage type, for a conversion would wait), then the rows, then what depends
+    // on the tile's slots. Asked for one after the other, each cost a memory latency.
+    const bool first_lane = kShifted ? i0 == 0 : (lane == 0 || lc == 0);
+    const bool last_lane = (!kShifted && (lane == 63 || lc == tpr - 1)) || last < V;
+    S left[3], right[3];
+    if (MODE != AA_LOCAL && act && first_lane) {
+        if (!kShifted && i0 > 0) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) left[m] = src[EXP[m] * P + row_of[EXP[m]] + (i0 - 1)];
+        } else {
+            side_column<MODE, false>(src, row_of, j, jm, jp, a, left);
+        }
+    }
+    if (MODE != AA_LOCAL && act && last_lane) {
+        if (!kShifted && last >= V) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) right[m] = src[EXM[m] * P + row_of[EXM[m]] + (i0 + V)];
+        } else {
+            side_column<MODE, true>(src, row_of, j, jm, jp, a, right);
+        }
+    }
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         S raw[V];
@@ -167,6 +168,26 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
 #pragma unroll
         for (int k = 0; k < V; ++k) v[q][k] = as_lv<LV>(raw[k]);
     }
+    // the slots list every body with a node in the tile: with none, the tile's
+    // mask is not read at all; with one, its row serves every solid node of the tile
+    if (s1 - s0 == 1) {
+        bs.uniform = true;
+        bs.row = body_row(a.bodies + BODY_STRIDE * a.slot_body[s0]);
+    }
+    if constexpr (MOVING) {
+        if (bs.pose) {   // once per tile: most tiles meet no moving body
+            // only the bodies the tile's slots list can reach it during the
+            // pose window (none for most tiles); of those, the ones whose
+            // radius about this step's centre meets the tile
+            uint32_t listed = 0;
+            for (int s = s0; s < s1; ++s) listed |= 1u << (a.slot_body[s] - 1);
+            if (listed) {
+                const double x0 = (double)(tx * a.tile_w), y0 = (double)(ty * a.tile_rows);
+                bs.near = listed & __builtin_amdgcn_readfirstlane(tile_near_bodies(
+                                       a, bs.pose, x0, x0 + (double)(a.tile_w - 1), y0, y0 + (double)(a.tile_rows - 1)));
+            }
+        }
+    }
     if (MOVING && bs.pose) {
 #pragma unroll
         for (int k = 0; k < V; ++k) body[k] = (k < n_own) ? moving_body(a, bs.pose, bs.near, i0 + k, j) : 0;
@@ -177,44 +198,35 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
         for (int k = 0; k < V; ++k) body[k] = 0;
     }
 
-    // the end elements of the x-shifted directions (lane-shuffle form only)
-    R left[3], right[3];
+    // the columns next to the thread's own, put where the nodes below take them
+    R from_left[3], from_right[3];
     if constexpr (!kShifted) {
 #pragma unroll
         for (int m = 0; m < 3; ++m) {
-            left[m] = wave_shift_up1(dec(v[EXP[m]][V - 1]));
-            right[m] = wave_shift_down1(dec(v[EXM[m]][0]));
+            const R l = wave_shift_up1(dec(v[EXP[m]][V - 1]));
+            from_left[m] = first_lane ? dec(left[m]) : l;
         }
-        // lanes that start a wavefront or a tile row load the end element
-        // themselves: a plain load inside the domain, the side resolution only
-        // where the column lies outside it
-        if (act && (lane == 0 || lc == 0)) {
-            if (i0 > 0) {
+        if (last < V - 1) {   // a row that ends inside the vector
 #pragma unroll
-                for (int m = 0; m < 3; ++m) left[m] = dec(src[EXP[m] * P + row_of[EXP[m]] + (i0 - 1)]);
-            } else {
+            for (int m = 0; m < 3; ++m)
 #pragma unroll
-                for (int m = 0; m < 3; ++m)
-                    left[m] = pull_column<MODE, S, R>(src, EXP[m], EXP[m], row_of[EXP[m]], row_idx[EXP[m]], -1, a);
-            }
+                for (int k = 1; k < V; ++k) v[EXM[m]][k] = k - 1 == last ? right[m] : v[EXM[m]][k];
         }
-        if (act && (lane == 63 || lc == tpr - 1)) {
-            if (i0 + V < a.nx) {
 #pragma unroll
-                for (int m = 0; m < 3; ++m) right[m] = dec(src[EXM[m] * P + row_of[EXM[m]] + (i0 + V)]);
-            } else {
-#pragma unroll
-                for (int m = 0; m < 3; ++m)
-                    right[m] = pull_column<MODE, S, R>(src, EXM[m], EXM[m], row_of[EXM[m]], row_idx[EXM[m]], i0 + V, a);
-            }
+        for (int m = 0; m < 3; ++m) {
+            const R r = wave_shift_down1(dec(v[EXM[m]][0]));
+            from_right[m] = last_lane ? dec(right[m]) : r;
         }
-    } else {
-        if (MODE != AA_LOCAL && act && i0 == 0) {  // the west side: column -1 is outside
+    } else if (MODE != AA_LOCAL) {
+        if (first_lane) {
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const int q = EXP[m];
-                v[q][0] = pull_column<MODE, S, R>(src, q, MODE == AA_PUSH ? OPP[q] : q, row_of[q], row_idx[q], -1, a);
-            }
+            for (int m = 0; m < 3; ++m) v[EXP[m]][0] = as_lv<LV>(left[m]);
+        }
+        if (last_lane) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int k = 0; k < V; ++k) v[EXM[m]][k] = k == last ? as_lv<LV>(right[m]) : v[EXM[m]][k];
         }
     }
 
@@ -230,18 +242,11 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
         if constexpr (!kShifted) {
 #pragma unroll
             for (int m = 0; m < 3; ++m) {
-                f[EXP[m]] = (k == 0) ? left[m] : dec(v[EXP[m]][k > 0 ? k - 1 : 0]);
-                f[EXM[m]] = (k == V - 1) ? right[m] : dec(v[EXM[m]][k < V - 1 ? k + 1 : 0]);
+                f[EXP[m]] = (k == 0) ? from_left[m] : dec(v[EXP[m]][k > 0 ? k - 1 : 0]);
+                f[EXM[m]] = (k == V - 1) ? from_right[m] : dec(v[EXM[m]][k < V - 1 ? k + 1 : 0]);
             }
         }
         const int i = i0 + k;
-        if (MODE != AA_LOCAL && i == a.nx - 1) {  // the east side: the neighbour column is outside
-#pragma unroll
-            for (int m = 0; m < 3; ++m) {
-                const int q = EXM[m];
-                f[q] = pull_column<MODE, S, R>(src, q, MODE == AA_PUSH ? OPP[q] : q, row_of[q], row_idx[q], a.nx, a);
-            }
-        }
         NodeResult<R> n;
         if constexpr (sizeof(S) == 2) {
             n = collide_node_lowp<R, MOVING>(f, body[k], i, j, a, bs);
@@ -396,19 +401,7 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
         double* slot_force = a.slot_force + part_buf * a.fin.slot_stride;
         const double wm = wave_sum_lane63(tile_drho);
         if (lane == 63) mass_part[(int64_t)t * (a.block >> 6) + (threadIdx.x >> 6)] = wm;
-        // forces: only tiles that hold solid nodes (uniform across the block);
-        // the body ids are read again (cache hit) rather than kept live
-        int bid[V];
-#pragma unroll
-        for (int k = 0; k < V; ++k) bid[k] = 0;
-        if (s1 > s0 && act) {
-            if (MOVING && bs.pose) {
-#pragma unroll
-                for (int k = 0; k < V; ++k) bid[k] = (k < n_own) ? moving_body(a, bs.pose, bs.near, i0 + k, j) : 0;
-            } else {
-                load_mask<V>(a.mask + r0 + i0, bid);
-            }
-        }
+        // forces: only tiles that hold solid nodes (uniform across the block)
         // each (tile, body) slot: every wavefront sums its lanes with DPP moves
         // into lane 63, which parks the sum in LDS; after one barrier per batch
         // of slots the block's first threads add the wavefronts in order
@@ -428,7 +421,7 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
                     double px = 0.0, py = 0.0;
 #pragma unroll
                     for (int k = 0; k < V; ++k) {
-                        if (k < n_own && bid[k] == b) {
+                        if (k < n_own && body[k] == b) {
                             px -= (double)fv[k * a.block + (int)threadIdx.x];
                             py -= (double)fv[(V + k) * a.block + (int)threadIdx.x];
                         }
