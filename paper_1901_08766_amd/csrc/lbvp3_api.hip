@@ -273,6 +273,11 @@ namespace {
         if (e_ != hipSuccess) return (ctx)->hip_fail(e_, #call);          \
     } while (0)
 
+uint64_t lattice_bytes(const lbvp3_ctx* c)   // both
+{
+    return 2 * (uint64_t)c->L.rows * (uint64_t)c->L.lstride * storage_bytes(c->p.storage);
+}
+
 template <typename R>
 void fill_args(lbvp3_ctx* c, Step3Args<R>& a)
 {
@@ -289,6 +294,7 @@ void fill_args(lbvp3_ctx* c, Step3Args<R>& a)
     a.tiles_x = l.tiles_x;
     a.n_tiles = l.n_tiles;
     a.tiles_per_xcd = l.tiles_per_xcd;
+    a.keep_tiles = lbvp::keep_tiles(lattice_bytes(c), l.tiles_per_xcd);
     a.band_log2 = band_log2(l.band);
     a.west = p.bc_west;
     a.east = p.bc_east;
@@ -1069,6 +1075,9 @@ lbvp_status lbvp3_batch_step(lbvp3_batch* b, int64_t n_steps, uint32_t flags)
     L.tile_start = reinterpret_cast<const int32_t*>(b->dev + b->off_start);
     L.members = b->dev;
     L.n_members = n;
+    uint64_t bytes = 0;
+    for (const lbvp3_ctx* c : b->members) bytes += lattice_bytes(c);
+    L.keep_tiles = lbvp::keep_tiles(bytes, b->tiles_per_xcd);
     // steps k0 .. k0 + n - 1 of the call (the members' parity flips with k),
     // then the run's last record summed in one launch
     auto run = [&](int64_t k0, int64_t n_run, bool keep_last) -> lbvp_status {

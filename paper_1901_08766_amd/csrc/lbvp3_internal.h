@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "lbvp3.h"
+#include "lbvp_cache.h"
 
 namespace lbvp3 {
 
@@ -62,6 +63,7 @@ struct Step3Args {
     int32_t tiles_x, n_tiles, tiles_per_xcd;
     int32_t band_log2;              // block -> tile order (xcd_tile): -1 eighths, else bands of 2^band_log2 tiles
     int32_t west, east;             // lbvp_bc of the x sides
+    int32_t keep_tiles;             // how many of each XCD's tiles are stored plain (the rest non-temporal)
     int64_t pitch;                  // elements per population row, mask row and field row
     int64_t lstride;                // elements between lattice rows r and r + 1 (= 19 pitch)
     int64_t plane_f;                // elements between field planes (= ny nz pitch)
@@ -115,6 +117,7 @@ struct Batch3Launch {
     int32_t n_members;
     int32_t n_fin, n_add;           // leading blocks that sum slices, then those that add rows (one per
                                     // member): multiples of the 8 XCDs, or 0 with nothing to sum or add
+    int32_t keep_tiles;             // as in Step3Args, over all tiles
     const int32_t* tile_domain;     // [total_tiles] member of each tile
     const int32_t* tile_start;      // [n_members] first tile of each member
     const void* members;            // Member3<R>[n_members]

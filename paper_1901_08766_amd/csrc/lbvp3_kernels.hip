@@ -58,6 +58,7 @@ using lbvp::Pair;
 using lbvp::recip;
 using lbvp::store_one;
 using lbvp::store_vec;
+using lbvp::with_hint;
 using lbvp::wave_sum_lane63;
 using lbvp::xcd_tile;
 
@@ -186,7 +187,7 @@ __device__ __forceinline__ R* force_lds()
 template <typename S, int V, bool RECORD, bool FIELDS>
 __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restrict__ dst,
                                            const Step3Args<typename Arith<S>::R>& a, int t, int part_buf,
-                                           double* lds)
+                                           double* lds, bool nt)
 {
     using R = typename Arith<S>::R;
     const int n_rows = a.ny * a.nz;
@@ -333,16 +334,19 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
         if (e < n_own) tile_drho += (double)n.drho;
     }
 
-    if (n_own == V) {
+    with_hint(nt, [&](auto hint) {
+        constexpr bool NT = decltype(hint)::value;
+        if (n_own == V) {
 #pragma unroll
-        for (int q = 0; q < Q; ++q) store_vec<S, V>(dst + own_row + (int64_t)q * a.pitch + i0, out[q]);
-    } else if (n_own > 0) {   // the ragged end of a row
+            for (int q = 0; q < Q; ++q) store_vec<S, V, NT>(dst + own_row + (int64_t)q * a.pitch + i0, out[q]);
+        } else if (n_own > 0) {   // the ragged end of a row
 #pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (e < n_own)
+            for (int e = 0; e < V; ++e)
+                if (e < n_own)
 #pragma unroll
-                for (int q = 0; q < Q; ++q) store_one<S>(dst + own_row + (int64_t)q * a.pitch + i0 + e, out[q][e]);
-    }
+                    for (int q = 0; q < Q; ++q) store_one<S, NT>(dst + own_row + (int64_t)q * a.pitch + i0 + e, out[q][e]);
+        }
+    });
 
     if constexpr (FIELDS) {
         R* fb = a.fields + r0 + i0;
@@ -519,7 +523,7 @@ k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith
     }
     const int t = xcd_tile(a.tiles_per_xcd, a.band_log2, lead);
     if (t >= a.n_tiles) return;   // whole block
-    step3_body<S, V, RECORD, FIELDS>(src, dst, a, t, a.part_buf, lds);
+    step3_body<S, V, RECORD, FIELDS>(src, dst, a, t, a.part_buf, lds, ((int)blockIdx.x - lead) / N_XCD >= a.keep_tiles);
 }
 
 // Many domains in one launch: block -> (member, tile) through the tile map; each
@@ -561,7 +565,8 @@ __global__ void __launch_bounds__(256) k_step3_batch(Batch3Launch b)
     const int cur = md.cur ^ b.flip;
     const S* src = static_cast<const S*>(cur ? md.lat1 : md.lat0);
     S* dst = static_cast<S*>(cur ? md.lat0 : md.lat1);
-    step3_body<S, V, RECORD, FIELDS>(src, dst, md.a, t, b.part_buf, lds);
+    step3_body<S, V, RECORD, FIELDS>(src, dst, md.a, t, b.part_buf, lds,
+                                     ((int)blockIdx.x - b.n_fin - b.n_add) / N_XCD >= b.keep_tiles);
 }
 
 // The last records of an lbvp3_batch_step call.

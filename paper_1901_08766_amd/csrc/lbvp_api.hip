@@ -355,6 +355,12 @@ void inflow_ghost(const lbvp_params& p, double out[9])
     }
 }
 
+// of a pull step's two lattices
+uint64_t lattice_bytes(const lbvp_ctx* c)
+{
+    return 2 * (uint64_t)c->p.ny * (uint64_t)c->L.lstride * c->esize();
+}
+
 template <typename R>
 void fill_step_args(lbvp_ctx* c, StepArgs<R>& a)
 {
@@ -370,6 +376,7 @@ void fill_step_args(lbvp_ctx* c, StepArgs<R>& a)
     a.tiles_x = l.tiles_x;
     a.n_tiles = l.n_tiles;
     a.tiles_per_xcd = l.tiles_per_xcd;
+    a.keep_tiles = keep_tiles(lattice_bytes(c), l.tiles_per_xcd);
     a.band_log2 = band_log2(l.band);
     a.west = p.bc_west;
     a.east = p.bc_east;
@@ -727,6 +734,7 @@ MarchArgs march_args(const lbvp_ctx* c)
     m.rows = (int32_t)std::min<int64_t>((waves + MARCH_WAVES - 1) / MARCH_WAVES, MARCH_ROWS);
     m.n_chunks = (c->p.ny + m.rows - 1) / m.rows;
     m.per_xcd = (m.n_chunks * l.tiles_x + N_XCD - 1) / N_XCD;
+    m.keep = keep_tiles(lattice_bytes(c), m.per_xcd);
     return m;
 }
 
@@ -982,7 +990,12 @@ lbvp_status batch_run(lbvp_batch* b, int64_t step0, int64_t k0, int64_t n, bool 
     L.tile_start = reinterpret_cast<const int32_t*>(b->dev + b->off_tile_start);
     L.args = b->dev;
     L.off32 = 1;
-    for (const lbvp_ctx* c : b->members) L.off32 &= c->a32.off32;   // off32 does not depend on the precision
+    uint64_t bytes = 0;
+    for (const lbvp_ctx* c : b->members) {
+        L.off32 &= c->a32.off32;   // off32 does not depend on the precision
+        bytes += lattice_bytes(c);
+    }
+    L.keep_tiles = keep_tiles(bytes, b->tiles_per_xcd);
     bool pending = false;
     int32_t pending_buf = 0;
     for (int64_t k = k0; k < k0 + n; ++k) {

@@ -113,46 +113,70 @@ __device__ __forceinline__ void load_vec(const S* p, S (&out)[V])
     }
 }
 
-// Stores are non-temporal: the new lattice is not read again before the whole
-// domain has streamed through the caches, so it should not displace anything.
+// Stores of the lattice, non-temporal (NT) or plain. While all lattices of a
+// launch fit the last-level cache the next step reads them from there, and plain
+// stores leave them in it; beyond that they only displace what the step still
+// reads (keep_tiles).
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
-template <typename S, int V>
+template <bool NT, typename U>
+__device__ __forceinline__ void put(U* p, U r)
+{
+    if constexpr (NT) __builtin_nontemporal_store(r, p);
+    else *p = r;
+}
+
+template <typename S, int V, bool NT>
 __device__ __forceinline__ void store_vec(S* p, const S (&in)[V])
 {
     constexpr int B = V * (int)sizeof(S);
     if constexpr (B == 16) {
         u32x4_t r;
         __builtin_memcpy(&r, in, 16);
-        __builtin_nontemporal_store(r, reinterpret_cast<u32x4_t*>(p));
+        put<NT>(reinterpret_cast<u32x4_t*>(p), r);
     } else if constexpr (B == 8) {
         u32x2_t r;
         __builtin_memcpy(&r, in, 8);
-        __builtin_nontemporal_store(r, reinterpret_cast<u32x2_t*>(p));
+        put<NT>(reinterpret_cast<u32x2_t*>(p), r);
     } else if constexpr (B == 4) {
         uint32_t r;
         __builtin_memcpy(&r, in, 4);
-        __builtin_nontemporal_store(r, reinterpret_cast<uint32_t*>(p));
+        put<NT>(reinterpret_cast<uint32_t*>(p), r);
     } else if constexpr (B == 2) {
         uint16_t r;
         __builtin_memcpy(&r, in, 2);
-        __builtin_nontemporal_store(r, reinterpret_cast<uint16_t*>(p));
+        put<NT>(reinterpret_cast<uint16_t*>(p), r);
     } else {
 #pragma unroll
         for (int k = 0; k < V; ++k) p[k] = in[k];
     }
 }
 
-// One element, non-temporal like the vector stores. Every store of the lattice
-// carries the hint: where the compiler merges a vector path and an element path
-// into one store, it keeps only the hints both carry, and a plain element store
-// there once stripped it from all 19 stores of a 3-D step (7% slower).
-template <typename S>
+// One element, like the vector stores. Every store of a path carries the same
+// hint: where the compiler merges a vector path and an element path into one
+// store, it keeps only the hints both carry, and a plain element store there once
+// stripped it from all 19 stores of a 3-D step (7% slower).
+template <typename S, bool NT>
 __device__ __forceinline__ void store_one(S* p, S v)
 {
     const S tmp[1] = {v};
-    store_vec<S, 1>(p, tmp);
+    store_vec<S, 1, NT>(p, tmp);
+}
+
+// stores(true_type) for non-temporal stores, else stores(false_type); `nt` is
+// uniform. The two differ in an empty statement, so that the compiler does not
+// merge them into one path without the hint.
+template <typename F>
+__device__ __forceinline__ void with_hint(bool nt, F stores)
+{
+    if (nt) {
+        stores(std::true_type{});
+        asm volatile("; non-temporal");
+    } else {
+        stores(std::false_type{});
+        asm volatile("; kept");
+    }
 }
 
 // The same V elements starting one element off a 16-byte boundary: a single
@@ -326,11 +350,11 @@ __device__ __forceinline__ void store_vec_shifted(S* p, const S (&in)[V])
     if constexpr (B == 16) {
         u32x4_a4 r;
         __builtin_memcpy(&r, in, 16);
-        __builtin_nontemporal_store(r, reinterpret_cast<u32x4_a4*>(p));
+        *reinterpret_cast<u32x4_a4*>(p) = r;
     } else if constexpr (B == 8) {
         u32x2_a4 r;
         __builtin_memcpy(&r, in, 8);
-        __builtin_nontemporal_store(r, reinterpret_cast<u32x2_a4*>(p));
+        *reinterpret_cast<u32x2_a4*>(p) = r;
     } else {
 #pragma unroll
         for (int k = 0; k < V; ++k) p[k] = in[k];

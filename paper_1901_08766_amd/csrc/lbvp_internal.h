@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "lbvp.h"
+#include "lbvp_cache.h"
 
 namespace lbvp {
 
@@ -68,6 +69,7 @@ struct StepArgs {
     int32_t fin_buf;    // partial buffer of the first record that leading blocks of the launch sum
     int32_t fin_n;      // how many records they sum (0: none), in consecutive buffers
     int32_t off32;      // a lattice spans fewer than 2^32 bytes: per-lane offsets fit 32 bits
+    int32_t keep_tiles; // how many of each XCD's tiles a pull step stores plain (the rest non-temporal)
     int64_t pitch;      // elements per row of one population, of the mask and of a field
     int64_t plane;      // elements between the rows of populations q and q + 1 (= pitch)
     int64_t lstride;    // elements between lattice rows j and j + 1 (= 9 pitch)
@@ -120,6 +122,7 @@ constexpr int MARCH_WAVES = 3072;   // wavefronts of it the chip holds: 1024 SIM
 struct MarchArgs {
     int32_t rows, n_chunks;         // rows per chunk, chunks per strip
     int32_t per_xcd;                // ceil(chunks * strips / 8)
+    int32_t keep;                   // how many of those are stored plain (keep_tiles)
     int32_t rec;                    // bit 0: the first step records (partial buffer part_buf), bit 1: the
                                     // second (the buffer after it if the first does, else part_buf)
 };
@@ -136,6 +139,7 @@ struct BatchLaunch {
     int32_t fin_share;              // leading blocks per domain
     int32_t pose_k;                 // this launch's step within the run (moving bodies)
     int32_t off32;                  // every member's StepArgs::off32
+    int32_t keep_tiles;             // as in StepArgs, over all tiles
     const int32_t* tile_domain;     // [total_tiles] domain of each tile
     const int32_t* tile_start;      // [n_domains] first tile of each domain
     const void* args;               // StepArgs<R>[n_domains]

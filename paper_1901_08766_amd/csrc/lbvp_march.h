@@ -193,11 +193,11 @@ __device__ __forceinline__ void buffer_load(BufferRsrc b, T& x, uint32_t off, ui
     }
 }
 
-// The same stored, non-temporal.
-template <typename T>
+// The same stored, non-temporal (NT) or plain.
+template <bool NT_, typename T>
 __device__ __forceinline__ void buffer_store(BufferRsrc b, const T& x, uint32_t off, uint32_t soff)
 {
-    constexpr int NT = 2;
+    constexpr int NT = NT_ ? 2 : 0;
     if constexpr (sizeof(T) == 16) {
         u32x4_t r;
         __builtin_memcpy(&r, &x, 16);
@@ -333,7 +333,7 @@ __device__ __forceinline__ void record_tile(const KernelArgs<R>& args, bool on, 
     double* mass_part = a->mass_part + buf * a->fin.mass_stride;
     const int lane = (int)(threadIdx.x & 63), wid = (int)threadIdx.x >> 6;
     const double wm = wave_sum_lane63(drho);
-    buffer_store(buffer_at(mass_part + (int64_t)t * nw, (uint32_t)nw * 8), wm,
+    buffer_store<true>(buffer_at(mass_part + (int64_t)t * nw, (uint32_t)nw * 8), wm,
                  on && lane == 63 ? (uint32_t)wid * 8 : NOWHERE, 0);
     if (!on || s1 <= s0) return;
     double* slot_force = a->slot_force + buf * a->fin.slot_stride;
@@ -667,14 +667,17 @@ k_march(const S* __restrict__ src, S* __restrict__ dst, StepArgs<typename Arith<
         S out[9][V];
         const double drho = row_nodes<S, V, RECORD>(held, out, pmask, (int)i0, y, n_own, ragged, a, fv);
         const BufferRsrc row = buffer_at(dst + drow, 9 * pop_bytes);
+        with_hint(blk / N_XCD >= m.keep, [&](auto hint) {
+            constexpr bool NT = decltype(hint)::value;
 #pragma unroll
-        for (int q = 0; q < 9; ++q) buffer_store(row, out[q], store_off, (uint32_t)q * pop_bytes);
+            for (int q = 0; q < 9; ++q) buffer_store<NT>(row, out[q], store_off, (uint32_t)q * pop_bytes);
+        });
         if (ragged) {   // the last columns of a row that ends inside a vector
 #pragma unroll
             for (int k = 0; k < V; ++k)
                 if (k < opaque(n_own) && n_own < V)
 #pragma unroll
-                    for (int q = 0; q < 9; ++q) store_one<S>(at_off32(dst + (drow + q * P + k), i0), out[q][k]);
+                    for (int q = 0; q < 9; ++q) store_one<S, true>(at_off32(dst + (drow + q * P + k), i0), out[q][k]);
         }
         drow = uniform(drow + a.lstride);
         if constexpr (RECORD)
