@@ -42,7 +42,6 @@ namespace {
 
 using lbvp::Arith;
 using lbvp::as_lv;
-using lbvp::block_sum;
 using lbvp::collide_pair;
 using lbvp::dec;
 using lbvp::div36;
@@ -160,20 +159,24 @@ __device__ __forceinline__ Node3<R> collide3(R (&f)[Q], int body, int i, int j, 
     return out;
 }
 
-// Population q pulled from column c of the lattice row at row_off, with the x
-// sides resolved (c = -1 or nx lies outside the domain). Inflow populations are
-// rounded to the storage type like every stored population.
-template <typename S, typename R>
-__device__ __forceinline__ R pull_col(const S* src, int q, int64_t row_off, int c, const Step3Args<R>& a)
+// What a boundary column (EAST: the last) pulls from the column outside the
+// domain: the populations with CX = 1 of a west side, CX = -1 of an east one.
+// Inflow populations are rounded to the storage type like every stored population.
+template <bool EAST, typename S, typename R>
+__device__ __forceinline__ void side_column(const S* src, const int64_t (&src_row)[Q], const Step3Args<R>& a, S (&e)[Q])
 {
-    if (c < 0) {
-        if (a.west == LBVP_BC_INFLOW_EQ) return dec(enc<S>(a.feq_in[q]));
-        c = (a.west == LBVP_BC_PERIODIC) ? a.nx - 1 : 0;
-    } else if (c >= a.nx) {
-        if (a.east == LBVP_BC_INFLOW_EQ) return dec(enc<S>(a.feq_in[q]));
-        c = (a.east == LBVP_BC_PERIODIC) ? 0 : a.nx - 1;
+    const int side = EAST ? a.east : a.west;
+    constexpr int SIGN = EAST ? -1 : 1;
+    if (side == LBVP_BC_INFLOW_EQ) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (CX[q] == SIGN) e[q] = enc<S>(a.feq_in[q]);
+    } else {
+        const int c = (EAST == (side == LBVP_BC_PERIODIC)) ? 0 : a.nx - 1;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            if (CX[q] == SIGN) e[q] = src[src_row[q] + (int64_t)q * a.pitch + c];
     }
-    return dec(src[row_off + (int64_t)q * a.pitch + c]);
 }
 
 template <typename R>
@@ -182,6 +185,9 @@ __device__ __forceinline__ R* force_lds()
     extern __shared__ __align__(16) unsigned char lds3_dyn[];
     return reinterpret_cast<R*>(lds3_dyn);
 }
+
+// lds: three sums per slot and wavefront of a batch of slots.
+constexpr int SLOT_PASS = 8;
 
 // Tile t: tile_rows lattice rows of tile_w nodes, V consecutive nodes per thread.
 template <typename S, int V, bool RECORD, bool FIELDS>
@@ -214,9 +220,8 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
     const int64_t own_row = (int64_t)row * a.lstride;
     const int64_t r0 = (int64_t)row * a.pitch;       // mask and fields
 
-    // this tile's (tile, body) force slots: loaded first, so that waiting for them
-    // never waits for the stores (a vector-memory wait covers every earlier
-    // access); a tile without slots holds no solid node and reads no mask
+    // this tile's (tile, body) force slots, asked for first; a tile without slots
+    // holds no solid node and reads no mask
     const int s0 = a.tile_slot_ptr[t];
     const int s1 = a.tile_slot_ptr[t + 1];
     // Dword-or-wider elements (and single nodes) fetch the x-shifted directions
@@ -227,14 +232,41 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
     constexpr bool kShifted = sizeof(S) >= 4 || V == 1;
     using LV = typename std::conditional<kShifted, R, S>::type;
     const int lane = (int)(threadIdx.x & 63);
-    LV v[Q][V];
     int body[V];
-    // 2-byte storage: threads without a node of their own load column 0 of
-    // their (clamped) row instead (every access stays inside the lattice; their
-    // results are never stored, summed or shuffled into an owned node), which
-    // spares the register clearing (1.5% faster); the wider types keep the branch
-    const int il = act ? i0 : 0;
-    if (sizeof(S) == 2 || act) {
+    double tile_drho = 0.0;
+    // a wavefront without a node only takes its part in the record: with 256 threads
+    // and rows of 192 nodes, one of four
+    if (__builtin_amdgcn_ballot_w64(act) != 0) {
+        LV v[Q][V];
+        // Threads without a node of their own load column 0 of their (clamped) row
+        // instead: every access stays inside the lattice, and their results are never
+        // stored, summed or shuffled into an owned node.
+        const int il = act ? i0 : 0;
+        const int last = a.nx - 1 - i0;   // this thread's index of the last column, if 0 .. V - 1
+        // As in the 2-D step, everything is requested before anything is waited for:
+        // the columns next to a thread's own (in the storage type), the rows, then
+        // what depends on the slots.
+        const bool first_lane = kShifted ? i0 == 0 : (lane == 0 || lc == 0);
+        const bool last_lane = (!kShifted && (lane == 63 || lc == tpr - 1)) || last < V;
+        S left[Q], right[Q];
+        if (act && first_lane) {
+            if (!kShifted && i0 > 0) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if (CX[q] == 1) left[q] = src[src_row[q] + (int64_t)q * a.pitch + (i0 - 1)];
+            } else {
+                side_column<false>(src, src_row, a, left);
+            }
+        }
+        if (act && last_lane) {
+            if (!kShifted && last >= V) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if (CX[q] == -1) right[q] = src[src_row[q] + (int64_t)q * a.pitch + (i0 + V)];
+            } else {
+                side_column<true>(src, src_row, a, right);
+            }
+        }
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             S raw[V];
@@ -255,132 +287,143 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
 #pragma unroll
             for (int e = 0; e < V; ++e) body[e] = 0;
         }
-        if constexpr (kShifted) {
-            if (il == 0) {   // the west side: column -1 lies outside
+
+        // the columns next to the thread's own, put where the nodes below take them
+        R from_left[Q], from_right[Q];
+        if constexpr (!kShifted) {
+            if (last < V - 1) {   // a row that ends inside the vector
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
-                    if (CX[q] == 1) v[q][0] = pull_col<S, R>(src, q, src_row[q], -1, a);
+                    if (CX[q] == -1)
+#pragma unroll
+                        for (int e = 1; e < V; ++e) v[q][e] = e - 1 == last ? right[q] : v[q][e];
+            }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                if (CX[q] == 1) {
+                    const R l = __shfl_up(dec(v[q][V - 1]), 1, 64);
+                    from_left[q] = first_lane ? dec(left[q]) : l;
+                }
+                if (CX[q] == -1) {
+                    const R r = __shfl_down(dec(v[q][0]), 1, 64);
+                    from_right[q] = last_lane ? dec(right[q]) : r;
+                }
+            }
+        } else {
+            if (first_lane) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if (CX[q] == 1) v[q][0] = as_lv<LV>(left[q]);
+            }
+            if (last_lane) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q)
+                    if (CX[q] == -1)
+#pragma unroll
+                        for (int e = 0; e < V; ++e) v[q][e] = e == last ? as_lv<LV>(right[q]) : v[q][e];
             }
         }
-    } else {
-#pragma unroll
-        for (int q = 0; q < Q; ++q)
-#pragma unroll
-            for (int e = 0; e < V; ++e) v[q][e] = LV{};
-#pragma unroll
-        for (int e = 0; e < V; ++e) body[e] = 0;
-    }
 
-    // the end elements of the x-shifted directions (lane-shuffle form only)
-    R left[Q], right[Q];
-    if constexpr (!kShifted) {
+        R fl[7][V];
+        S out[Q][V];
 #pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            if (CX[q] == 1) left[q] = __shfl_up(dec(v[q][V - 1]), 1, 64);
-            if (CX[q] == -1) right[q] = __shfl_down(dec(v[q][0]), 1, 64);
-        }
-        if (act && (lane == 0 || lc == 0)) {
+        for (int e = 0; e < V; ++e) {
+            R f[Q];
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (CX[q] == 1) left[q] = pull_col<S, R>(src, q, src_row[q], i0 - 1, a);
-        }
-        if (act && (lane == 63 || lc == tpr - 1)) {
-#pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (CX[q] == -1) right[q] = pull_col<S, R>(src, q, src_row[q], i0 + V, a);
-        }
-    }
-
-    R fl[7][V];
-    double tile_drho = 0.0;
-    S out[Q][V];
-#pragma unroll
-    for (int e = 0; e < V; ++e) {
-        R f[Q];
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            if constexpr (kShifted) {
-                f[q] = v[q][e];
-            } else {
-                if (CX[q] == 1) f[q] = (e == 0) ? left[q] : dec(v[q][e > 0 ? e - 1 : 0]);
-                else if (CX[q] == -1) f[q] = (e == V - 1) ? right[q] : dec(v[q][e < V - 1 ? e + 1 : 0]);
-                else f[q] = dec(v[q][e]);
+            for (int q = 0; q < Q; ++q) {
+                if constexpr (kShifted) {
+                    f[q] = v[q][e];
+                } else {
+                    if (CX[q] == 1) f[q] = (e == 0) ? from_left[q] : dec(v[q][e > 0 ? e - 1 : 0]);
+                    else if (CX[q] == -1) f[q] = (e == V - 1) ? from_right[q] : dec(v[q][e < V - 1 ? e + 1 : 0]);
+                    else f[q] = dec(v[q][e]);
+                }
             }
-        }
-        const int i = i0 + e;
-        if (i == a.nx - 1) {   // the east side: column nx lies outside
+            const int i = i0 + e;
+            const Node3<R> n = collide3<R, (sizeof(S) >= 4)>(f, body[e], i, j, k, a);
 #pragma unroll
-            for (int q = 0; q < Q; ++q)
-                if (CX[q] == -1) f[q] = pull_col<S, R>(src, q, src_row[q], a.nx, a);
-        }
-        const Node3<R> n = collide3<R, (sizeof(S) >= 4)>(f, body[e], i, j, k, a);
+            for (int q = 0; q < Q; ++q) out[q][e] = enc<S>(f[q]);
+            fl[0][e] = n.rho;
 #pragma unroll
-        for (int q = 0; q < Q; ++q) out[q][e] = enc<S>(f[q]);
-        fl[0][e] = n.rho;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            fl[1 + d][e] = n.u[d];
-            fl[4 + d][e] = n.fv[d];
-        }
-        if constexpr (RECORD) {
-            // the penalization force of every node of a tile holding solid nodes
-            // goes to LDS at once, summed per body after the stores
-            if (s1 > s0) {
-                R* fv = force_lds<R>();
-#pragma unroll
-                for (int c = 0; c < 3; ++c) fv[(c * V + e) * (int)blockDim.x + (int)threadIdx.x] = n.fv[c];
+            for (int d = 0; d < 3; ++d) {
+                fl[1 + d][e] = n.u[d];
+                fl[4 + d][e] = n.fv[d];
             }
-        }
-        if (e < n_own) tile_drho += (double)n.drho;
-    }
-
-    with_hint(nt, [&](auto hint) {
-        constexpr bool NT = decltype(hint)::value;
-        if (n_own == V) {
+            if constexpr (RECORD) {
+                // the penalization force of every node of a tile holding solid nodes
+                // goes to LDS at once, summed per body after the stores
+                if (s1 > s0) {
+                    R* fv = force_lds<R>();
 #pragma unroll
-            for (int q = 0; q < Q; ++q) store_vec<S, V, NT>(dst + own_row + (int64_t)q * a.pitch + i0, out[q]);
-        } else if (n_own > 0) {   // the ragged end of a row
+                    for (int c = 0; c < 3; ++c) fv[(c * V + e) * (int)blockDim.x + (int)threadIdx.x] = n.fv[c];
+                }
+            }
+            if (e < n_own) tile_drho += (double)n.drho;
+        }
+
+        with_hint(nt, [&](auto hint) {
+            constexpr bool NT = decltype(hint)::value;
+            if (n_own == V) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) store_vec<S, V, NT>(dst + own_row + (int64_t)q * a.pitch + i0, out[q]);
+            } else if (n_own > 0) {   // the ragged end of a row
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                    if (e < n_own)
+#pragma unroll
+                        for (int q = 0; q < Q; ++q) store_one<S, NT>(dst + own_row + (int64_t)q * a.pitch + i0 + e, out[q][e]);
+            }
+        });
+
+        if constexpr (FIELDS) {
+            R* fb = a.fields + r0 + i0;
 #pragma unroll
             for (int e = 0; e < V; ++e)
                 if (e < n_own)
 #pragma unroll
-                    for (int q = 0; q < Q; ++q) store_one<S, NT>(dst + own_row + (int64_t)q * a.pitch + i0 + e, out[q][e]);
+                    for (int c = 0; c < 7; ++c) fb[c * a.plane_f + e] = fl[c][e];
         }
-    });
-
-    if constexpr (FIELDS) {
-        R* fb = a.fields + r0 + i0;
+    } else {
 #pragma unroll
-        for (int e = 0; e < V; ++e)
-            if (e < n_own)
-#pragma unroll
-                for (int c = 0; c < 7; ++c) fb[c * a.plane_f + e] = fl[c][e];
+        for (int e = 0; e < V; ++e) body[e] = 0;
     }
 
     if constexpr (RECORD) {
         // mass: one partial per wavefront (DPP moves only, no block barrier)
-        const int lane = (int)(threadIdx.x & 63);
         const double wm = wave_sum_lane63(tile_drho);
         double* mass_part = a.mass_part + part_buf * a.fin.mass_stride;
         double* slot_force = a.slot_force + part_buf * a.fin.slot_stride;
         if (lane == 63) mass_part[(int64_t)t * (a.block >> 6) + (threadIdx.x >> 6)] = wm;
-        if (s1 > s0) {   // tiles that hold solid nodes (uniform across the block)
-            const R* fv = force_lds<R>();
-            const int nt = (int)blockDim.x;
-            for (int s = s0; s < s1; ++s) {
+        // forces: only tiles that hold solid nodes (uniform across the block); each
+        // slot's wavefront sums meet in LDS, a batch of slots per barrier, and are
+        // added in wavefront order
+        const R* fv = force_lds<R>();
+        const int block = (int)blockDim.x, nw = block >> 6, wid = (int)threadIdx.x >> 6;
+        for (int c0 = s0; c0 < s1; c0 += SLOT_PASS) {
+            const int c1 = min(s1, c0 + SLOT_PASS);
+            for (int s = c0; s < c1; ++s) {
                 const int b = a.slot_body[s];
                 double p[3] = {0.0, 0.0, 0.0};
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     if (e < n_own && body[e] == b)
 #pragma unroll
-                        for (int c = 0; c < 3; ++c) p[c] -= (double)fv[(c * V + e) * nt + (int)threadIdx.x];
+                        for (int c = 0; c < 3; ++c) p[c] -= (double)fv[(c * V + e) * block + (int)threadIdx.x];
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const double sum = block_sum(p[c], lds);
-                    if (threadIdx.x == 0) slot_force[3 * s + c] = sum;
-                }
+                for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) p[c] += __shfl_down(p[c], off, 64);
+                if (lane == 0)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) lds[(3 * (s - c0) + c) * nw + wid] = p[c];
             }
+            __syncthreads();
+            for (int i = (int)threadIdx.x; i < 3 * (c1 - c0); i += block) {
+                double x = lds[i * nw];
+                for (int w = 1; w < nw; ++w) x += lds[i * nw + w];
+                slot_force[3 * c0 + i] = x;
+            }
+            __syncthreads();   // lds is reused by the next batch of slots
         }
     }
 }
@@ -513,7 +556,7 @@ template <typename S, int V, bool RECORD, bool FIELDS>
 __global__ void __launch_bounds__(256)
 k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith<S>::R> a)
 {
-    __shared__ double lds[4];   // per-wavefront sums of block_sum
+    __shared__ double lds[3 * SLOT_PASS * 4];
     const int n_fin = a.fin_buf >= 0 ? slice_blocks(1, a.block) : 0;
     const int lead = n_fin + (a.add_stage >= 0 ? N_XCD : 0);
     if ((int)blockIdx.x < lead) {
@@ -534,7 +577,7 @@ template <typename S, int V, bool RECORD, bool FIELDS>
 __global__ void __launch_bounds__(256) k_step3_batch(Batch3Launch b)
 {
     using R = typename Arith<S>::R;
-    __shared__ double lds[4];
+    __shared__ double lds[3 * SLOT_PASS * 4];
     const Member3<R>* m = static_cast<const Member3<R>*>(b.members);
     if ((int)blockIdx.x < b.n_fin + b.n_add) {
         const int blk = (int)blockIdx.x;
