@@ -592,8 +592,7 @@ lbvp_status lbvp3_set_mask(lbvp3_ctx* c, const uint8_t* body_id, int32_t n_bodie
     c->bodies_host.assign(bodies, bodies + n_bodies);
     c->n_bodies = n_bodies;
     hipStream_t s = c->stream;
-    LBVP3_HIP(c, hipMemcpy2DAsync(c->at<uint8_t>(L.mask), (size_t)L.pitch, c->mask_host.data(), (size_t)p.nx,
-                                  (size_t)p.nx, (size_t)L.rows, hipMemcpyHostToDevice, s));
+    LBVP3_HIP(c, lbvp::write_mask(s, c->at<uint8_t>(L.mask), L.pitch, p.nx, L.rows, c->mask_host.data()));
     LBVP3_HIP(c, hipMemcpyAsync(c->at<char>(L.bodies), table.data(), table.size(), hipMemcpyHostToDevice, s));
     return apply_launch(c, c->launch);   // synchronizes
 }

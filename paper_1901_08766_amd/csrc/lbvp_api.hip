@@ -1420,8 +1420,7 @@ lbvp_status lbvp_set_mask(lbvp_ctx* c, const uint8_t* body_id, int32_t n_bodies,
     c->gen += 1;
 
     hipStream_t s = c->stream;
-    LBVP_HIP(c, hipMemcpy2DAsync(c->at<uint8_t>(L.mask), (size_t)L.pitch, body_id, (size_t)p.nx,
-                                 (size_t)p.nx, (size_t)p.ny, hipMemcpyHostToDevice, s));
+    LBVP_HIP(c, write_mask(s, c->at<uint8_t>(L.mask), L.pitch, p.nx, p.ny, body_id));
     LBVP_HIP(c, hipMemcpyAsync(c->at<char>(L.bodies), table.data(), table.size(), hipMemcpyHostToDevice, s));
     return build_tile_tables(c);  // synchronizes
 }

@@ -1,5 +1,5 @@
-// lbvp_readback.h -- field planes from the device to host doubles, shared by the
-// D2Q9 and D3Q19 read calls.
+// lbvp_readback.h -- field planes from the device to host doubles and masks from
+// the host to pitched device rows, shared by the D2Q9 and D3Q19 calls.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,7 +16,12 @@ constexpr int MAX_READ_PLANES = 7;
 hipError_t read_planes(hipStream_t s, bool is_f64, const void* base, const int64_t* off, int n, int64_t pitch,
                        int32_t nx, int64_t rows, double* const* dst);
 
-// The pinned staging buffers that read_planes uses are kept between calls while
+// Writes `rows` rows of nx bytes, back to back at src, to device rows of `pitch`
+// bytes (the rest of a row is left as it is). Enqueues on s; src has been read
+// when it returns.
+hipError_t write_mask(hipStream_t s, uint8_t* dst, int64_t pitch, int32_t nx, int64_t rows, const uint8_t* src);
+
+// The pinned staging buffers that both use are kept between calls while
 // any context lives: every context counts itself in and out.
 void readback_retain();
 void readback_release();
