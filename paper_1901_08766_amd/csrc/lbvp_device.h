@@ -264,25 +264,31 @@ __device__ __forceinline__ double block_sum(double v, double* lds)
 
 // ------------------------------------------------------------ the collision --
 // Quotients that must not carry a fixed relative error (a biased 1/36 or 1/rho
-// would bias every collision's momentum, which a decaying flow accumulates): FP64
-// divides; FP32 multiplies by the rounded reciprocal and corrects with the exact
-// residual (one FMA), which returns the quotient to within a hair of correct
-// rounding with no systematic direction, in 3 instructions instead of ~10.
-__device__ __forceinline__ double div36(double s) { return s / 36.0; }
-__device__ __forceinline__ float div36(float s)
+// would bias every collision's momentum, which a decaying flow accumulates):
+// multiplied by the rounded reciprocal and corrected with the exact residual (one
+// FMA). In FP64 that is the correctly rounded quotient (Markstein: the reciprocal is
+// correctly rounded and the first quotient within an ulp), in 3 instructions
+// instead of the division's 11; in FP32 it is within a hair of it, with no
+// systematic direction. 1/x: the hardware's approximation (22 bits or better in
+// FP64, ~1 ulp in FP32), Newton steps and the same last correction.
+template <int D, typename R>
+__device__ __forceinline__ R div_const(R s)
 {
-    const float r = 1.0f / 36.0f;
-    const float q = s * r;
-    return __builtin_fmaf(__builtin_fmaf(-36.0f, q, s), r, q);
+    const R r = R(1) / R(D);
+    const R q = s * r;
+    return fma(fma(R(-D), q, s), r, q);
 }
-__device__ __forceinline__ double div12(double s) { return s / 12.0; }
-__device__ __forceinline__ float div12(float s)
+template <typename R>
+__device__ __forceinline__ R div36(R s) { return div_const<36>(s); }
+template <typename R>
+__device__ __forceinline__ R div12(R s) { return div_const<12>(s); }
+__device__ __forceinline__ double recip(double x)
 {
-    const float r = 1.0f / 12.0f;
-    const float q = s * r;
-    return __builtin_fmaf(__builtin_fmaf(-12.0f, q, s), r, q);
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
 }
-__device__ __forceinline__ double recip(double x) { return 1.0 / x; }
 __device__ __forceinline__ float recip(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x);            // ~1 ulp
