@@ -295,6 +295,10 @@ void fill_args(lbvp3_ctx* c, Step3Args<R>& a)
     a.n_tiles = l.n_tiles;
     a.tiles_per_xcd = l.tiles_per_xcd;
     a.keep_tiles = lbvp::keep_tiles(lattice_bytes(c), l.tiles_per_xcd);
+    a.off32 = lattice_bytes(c) / 2 <= 0xFFFFFFFFull ? 1 : 0;
+    const uint32_t tpr = (uint32_t)(l.tile_w / l.vec);
+    a.tpr_mul = (65536u + tpr - 1) / tpr;
+    a.ny_mul = (uint32_t)(((uint64_t(1) << 32) + (uint32_t)p.ny - 1) / (uint32_t)p.ny);
     a.band_log2 = band_log2(l.band);
     a.west = p.bc_west;
     a.east = p.bc_east;
@@ -1075,7 +1079,11 @@ lbvp_status lbvp3_batch_step(lbvp3_batch* b, int64_t n_steps, uint32_t flags)
     L.members = b->dev;
     L.n_members = n;
     uint64_t bytes = 0;
-    for (const lbvp3_ctx* c : b->members) bytes += lattice_bytes(c);
+    L.off32 = 1;
+    for (const lbvp3_ctx* c : b->members) {
+        bytes += lattice_bytes(c);
+        L.off32 &= c->a32.off32;   // off32 does not depend on the precision
+    }
     L.keep_tiles = lbvp::keep_tiles(bytes, b->tiles_per_xcd);
     // steps k0 .. k0 + n - 1 of the call (the members' parity flips with k),
     // then the run's last record summed in one launch

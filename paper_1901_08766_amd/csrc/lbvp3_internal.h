@@ -64,6 +64,8 @@ struct Step3Args {
     int32_t band_log2;              // block -> tile order (xcd_tile): -1 eighths, else bands of 2^band_log2 tiles
     int32_t west, east;             // lbvp_bc of the x sides
     int32_t keep_tiles;             // how many of each XCD's tiles are stored plain (the rest non-temporal)
+    int32_t off32;                  // a lattice spans fewer than 2^32 bytes: per-lane offsets fit 32 bits
+    uint32_t tpr_mul, ny_mul;       // ceil(2^16 vec / tile_w), ceil(2^32 / ny)
     int64_t pitch;                  // elements per population row, mask row and field row
     int64_t lstride;                // elements between lattice rows r and r + 1 (= 19 pitch)
     int64_t plane_f;                // elements between field planes (= ny nz pitch)
@@ -118,6 +120,7 @@ struct Batch3Launch {
     int32_t n_fin, n_add;           // leading blocks that sum slices, then those that add rows (one per
                                     // member): multiples of the 8 XCDs, or 0 with nothing to sum or add
     int32_t keep_tiles;             // as in Step3Args, over all tiles
+    int32_t off32;                  // every member's Step3Args::off32
     const int32_t* tile_domain;     // [total_tiles] member of each tile
     const int32_t* tile_start;      // [n_members] first tile of each member
     const void* members;            // Member3<R>[n_members]

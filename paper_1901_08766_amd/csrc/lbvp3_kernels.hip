@@ -42,6 +42,7 @@ namespace {
 
 using lbvp::Arith;
 using lbvp::as_lv;
+using lbvp::at_off32;
 using lbvp::collide_pair;
 using lbvp::dec;
 using lbvp::div36;
@@ -159,11 +160,25 @@ __device__ __forceinline__ Node3<R> collide3(R (&f)[Q], int body, int i, int j, 
     return out;
 }
 
+// Population q of column c + shift of the lattice row at element row_off. A 32-bit
+// offset is the lane's own part of the address, on a base that is the same for all
+// lanes (c + row_off >= 0; a shift of -1 belongs to the base).
+template <typename S, typename R>
+__device__ __forceinline__ S* pop_at(S* lat, int q, int64_t row_off, int c, const Step3Args<R>& a, int shift = 0)
+{
+    return lat + (row_off + (int64_t)q * a.pitch + (c + shift));
+}
+template <typename S, typename R>
+__device__ __forceinline__ S* pop_at(S* lat, int q, uint32_t row_off, int c, const Step3Args<R>& a, int shift = 0)
+{
+    return at_off32(lat + ((int64_t)q * a.pitch + shift), row_off + (uint32_t)c);
+}
+
 // What a boundary column (EAST: the last) pulls from the column outside the
 // domain: the populations with CX = 1 of a west side, CX = -1 of an east one.
 // Inflow populations are rounded to the storage type like every stored population.
-template <bool EAST, typename S, typename R>
-__device__ __forceinline__ void side_column(const S* src, const int64_t (&src_row)[Q], const Step3Args<R>& a, S (&e)[Q])
+template <bool EAST, typename S, typename R, typename Off>
+__device__ __forceinline__ void side_column(const S* src, const Off (&src_row)[Q], const Step3Args<R>& a, S (&e)[Q])
 {
     const int side = EAST ? a.east : a.west;
     constexpr int SIGN = EAST ? -1 : 1;
@@ -175,7 +190,7 @@ __device__ __forceinline__ void side_column(const S* src, const int64_t (&src_ro
         const int c = (EAST == (side == LBVP_BC_PERIODIC)) ? 0 : a.nx - 1;
 #pragma unroll
         for (int q = 0; q < Q; ++q)
-            if (CX[q] == SIGN) e[q] = src[src_row[q] + (int64_t)q * a.pitch + c];
+            if (CX[q] == SIGN) e[q] = *pop_at(src, q, src_row[q], c, a);
     }
 }
 
@@ -190,7 +205,13 @@ __device__ __forceinline__ R* force_lds()
 constexpr int SLOT_PASS = 8;
 
 // Tile t: tile_rows lattice rows of tile_w nodes, V consecutive nodes per thread.
-template <typename S, int V, bool RECORD, bool FIELDS>
+// OFF32: a lattice spans fewer than 2^32 bytes, so a lane's offsets into it fit 32
+// bits and every access takes a scalar base and one of nine lane offsets. With one
+// node per thread the vector unit bounds the step, and the 38 64-bit addresses, the
+// products they came from and two divisions were a fifth of its 556 instructions: 5
+// FP16 domains in a batch 26.0 -> 23.4 us per step, FP32 192 x 104 x 104 (bound by
+// memory) 50.5 -> 50.2.
+template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
 __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restrict__ dst,
                                            const Step3Args<typename Arith<S>::R>& a, int t, int part_buf,
                                            double* lds, bool nt)
@@ -199,25 +220,31 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
     const int n_rows = a.ny * a.nz;
     const int ty = t / a.tiles_x, tx = t - ty * a.tiles_x;
     const int tpr = a.tile_w / V;
-    const int lr = (int)threadIdx.x / tpr, lc = (int)threadIdx.x - lr * tpr;
+    // quotients by multiplication: exact for threadIdx.x < 256; at most one too large for row
+    const int lr = (int)(((uint32_t)threadIdx.x * a.tpr_mul) >> 16), lc = (int)threadIdx.x - lr * tpr;
     const int row_u = ty * a.tile_rows + lr;
     const int row = min(row_u, n_rows - 1);          // rows past the grid idle (clamped for addressing)
-    const int k = row / a.ny, j = row - k * a.ny;
+    int k = (int)__umulhi((uint32_t)row, a.ny_mul), j = row - k * a.ny;
+    if (j < 0) {
+        k -= 1;
+        j += a.ny;
+    }
     const int i0 = tx * a.tile_w + lc * V;
     const bool act = i0 < a.nx && row_u < n_rows && lr < a.tile_rows;   // threads past the tile's rows idle
     const int n_own = act ? min(V, a.nx - i0) : 0;
 
-    const int jm = (j == 0) ? a.ny - 1 : j - 1, jp = (j == a.ny - 1) ? 0 : j + 1;   // y and z periodic
-    const int km = (k == 0) ? a.nz - 1 : k - 1, kp = (k == a.nz - 1) ? 0 : k + 1;
-    // the lattice row each direction pulls from: (y - e_y, z - e_z)
-    int64_t src_row[Q];
+    // the lattice row each direction pulls from, (y - e_y, z - e_z), as elements: y and
+    // z are periodic
+    using Off = typename std::conditional<OFF32, uint32_t, int64_t>::type;
+    const Off ls = (Off)a.lstride, zs = (Off)a.ny * ls;
+    const Off own_row = (Off)row * ls;
+    const Off y_up = j == 0 ? zs - ls : (Off)0 - ls, y_down = j == a.ny - 1 ? ls - zs : ls;
+    const Off z_up = k == 0 ? (Off)(a.nz - 1) * zs : (Off)0 - zs, z_down = k == a.nz - 1 ? (Off)0 - (Off)(a.nz - 1) * zs : zs;
+    Off src_row[Q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int y = CY[q] == 1 ? jm : (CY[q] == -1 ? jp : j);
-        const int z = CZ[q] == 1 ? km : (CZ[q] == -1 ? kp : k);
-        src_row[q] = ((int64_t)z * a.ny + y) * a.lstride;
-    }
-    const int64_t own_row = (int64_t)row * a.lstride;
+    for (int q = 0; q < Q; ++q)
+        src_row[q] = own_row + (CY[q] == 1 ? y_up : (CY[q] == -1 ? y_down : (Off)0)) +
+                     (CZ[q] == 1 ? z_up : (CZ[q] == -1 ? z_down : (Off)0));
     const int64_t r0 = (int64_t)row * a.pitch;       // mask and fields
 
     // this tile's (tile, body) force slots, asked for first; a tile without slots
@@ -253,7 +280,7 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
             if (!kShifted && i0 > 0) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
-                    if (CX[q] == 1) left[q] = src[src_row[q] + (int64_t)q * a.pitch + (i0 - 1)];
+                    if (CX[q] == 1) left[q] = *pop_at(src, q, src_row[q], i0 - 1, a);
             } else {
                 side_column<false>(src, src_row, a, left);
             }
@@ -262,7 +289,7 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
             if (!kShifted && last >= V) {
 #pragma unroll
                 for (int q = 0; q < Q; ++q)
-                    if (CX[q] == -1) right[q] = src[src_row[q] + (int64_t)q * a.pitch + (i0 + V)];
+                    if (CX[q] == -1) right[q] = *pop_at(src, q, src_row[q], i0 + V, a);
             } else {
                 side_column<true>(src, src_row, a, right);
             }
@@ -270,13 +297,12 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             S raw[V];
-            const S* p = src + src_row[q] + (int64_t)q * a.pitch;
             if constexpr (kShifted) {
-                if (CX[q] == 1) load_vec_shifted<S, V>(p + (il - 1), raw);
-                else if (CX[q] == -1) load_vec_shifted<S, V>(p + (il + 1), raw);
-                else load_vec<S, V>(p + il, raw);
+                const S* p = pop_at(src, q, src_row[q], il, a, -CX[q]);
+                if (CX[q] != 0) load_vec_shifted<S, V>(p, raw);
+                else load_vec<S, V>(p, raw);
             } else {
-                load_vec<S, V>(p + il, raw);
+                load_vec<S, V>(pop_at(src, q, src_row[q], il, a), raw);
             }
 #pragma unroll
             for (int e = 0; e < V; ++e) v[q][e] = as_lv<LV>(raw[e]);
@@ -365,13 +391,13 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
             constexpr bool NT = decltype(hint)::value;
             if (n_own == V) {
 #pragma unroll
-                for (int q = 0; q < Q; ++q) store_vec<S, V, NT>(dst + own_row + (int64_t)q * a.pitch + i0, out[q]);
+                for (int q = 0; q < Q; ++q) store_vec<S, V, NT>(pop_at(dst, q, own_row, i0, a), out[q]);
             } else if (n_own > 0) {   // the ragged end of a row
 #pragma unroll
                 for (int e = 0; e < V; ++e)
                     if (e < n_own)
 #pragma unroll
-                        for (int q = 0; q < Q; ++q) store_one<S, NT>(dst + own_row + (int64_t)q * a.pitch + i0 + e, out[q][e]);
+                        for (int q = 0; q < Q; ++q) store_one<S, NT>(pop_at(dst, q, own_row, i0 + e, a), out[q][e]);
             }
         });
 
@@ -552,7 +578,7 @@ __device__ __forceinline__ void finalize_run(const Fin3Args& f, int buf, int sta
 }
 
 // A step launch, behind the leading blocks that sum earlier records.
-template <typename S, int V, bool RECORD, bool FIELDS>
+template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
 __global__ void __launch_bounds__(256)
 k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith<S>::R> a)
 {
@@ -566,14 +592,14 @@ k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith
     }
     const int t = xcd_tile(a.tiles_per_xcd, a.band_log2, lead);
     if (t >= a.n_tiles) return;   // whole block
-    step3_body<S, V, RECORD, FIELDS>(src, dst, a, t, a.part_buf, lds, ((int)blockIdx.x - lead) / N_XCD >= a.keep_tiles);
+    step3_body<S, V, RECORD, FIELDS, OFF32>(src, dst, a, t, a.part_buf, lds, ((int)blockIdx.x - lead) / N_XCD >= a.keep_tiles);
 }
 
 // Many domains in one launch: block -> (member, tile) through the tile map; each
 // member's arguments and lattices live in device memory. The members step in
 // lockstep: one step kind, record flag and partial buffer for all; leading
 // blocks sum the members' earlier records.
-template <typename S, int V, bool RECORD, bool FIELDS>
+template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
 __global__ void __launch_bounds__(256) k_step3_batch(Batch3Launch b)
 {
     using R = typename Arith<S>::R;
@@ -608,7 +634,7 @@ __global__ void __launch_bounds__(256) k_step3_batch(Batch3Launch b)
     const int cur = md.cur ^ b.flip;
     const S* src = static_cast<const S*>(cur ? md.lat1 : md.lat0);
     S* dst = static_cast<S*>(cur ? md.lat0 : md.lat1);
-    step3_body<S, V, RECORD, FIELDS>(src, dst, md.a, t, b.part_buf, lds,
+    step3_body<S, V, RECORD, FIELDS, OFF32>(src, dst, md.a, t, b.part_buf, lds,
                                      ((int)blockIdx.x - b.n_fin - b.n_add) / N_XCD >= b.keep_tiles);
 }
 
@@ -702,22 +728,30 @@ __global__ void __launch_bounds__(256) k_encode3(S* lat, Conv3Args a)
 
 __global__ void k_zero_i64(int64_t* p) { *p = 0; }
 
-template <typename S, int V>
-hipError_t step_v(bool record, bool fields, const S* in, S* out, const Step3Args<typename Arith<S>::R>& a,
-                  hipStream_t s)
+template <typename S, int V, bool OFF32>
+hipError_t step_off(bool record, bool fields, const S* in, S* out, const Step3Args<typename Arith<S>::R>& a,
+                    hipStream_t s)
 {
     using R = typename Arith<S>::R;
     const int lead = (a.fin_buf >= 0 ? slice_blocks(1, a.block) : 0) + (a.add_stage >= 0 ? N_XCD : 0);
     const dim3 grid((unsigned)(a.tiles_per_xcd * N_XCD + lead)), block((unsigned)a.block);
     const size_t lds = record ? 3 * (size_t)V * (size_t)a.block * sizeof(R) : 0;
     if (record) {
-        if (fields) hipLaunchKernelGGL((k_step3<S, V, true, true>), grid, block, lds, s, in, out, a);
-        else hipLaunchKernelGGL((k_step3<S, V, true, false>), grid, block, lds, s, in, out, a);
+        if (fields) hipLaunchKernelGGL((k_step3<S, V, true, true, OFF32>), grid, block, lds, s, in, out, a);
+        else hipLaunchKernelGGL((k_step3<S, V, true, false, OFF32>), grid, block, lds, s, in, out, a);
     } else {
-        if (fields) hipLaunchKernelGGL((k_step3<S, V, false, true>), grid, block, 0, s, in, out, a);
-        else hipLaunchKernelGGL((k_step3<S, V, false, false>), grid, block, 0, s, in, out, a);
+        if (fields) hipLaunchKernelGGL((k_step3<S, V, false, true, OFF32>), grid, block, 0, s, in, out, a);
+        else hipLaunchKernelGGL((k_step3<S, V, false, false, OFF32>), grid, block, 0, s, in, out, a);
     }
     return hipGetLastError();
+}
+
+template <typename S, int V>
+hipError_t step_v(bool record, bool fields, const S* in, S* out, const Step3Args<typename Arith<S>::R>& a,
+                  hipStream_t s)
+{
+    return a.off32 ? step_off<S, V, true>(record, fields, in, out, a, s)
+                   : step_off<S, V, false>(record, fields, in, out, a, s);
 }
 
 template <typename S>
@@ -741,20 +775,27 @@ hipError_t step_typed(bool record, bool fields, const void* src, void* dst, cons
     return hipErrorInvalidValue;
 }
 
-template <typename S, int V>
-hipError_t batch_v(bool record, bool fields, const Batch3Launch& b, int32_t block, hipStream_t s)
+template <typename S, int V, bool OFF32>
+hipError_t batch_off(bool record, bool fields, const Batch3Launch& b, int32_t block, hipStream_t s)
 {
     using R = typename Arith<S>::R;
     const dim3 grid((unsigned)(b.tiles_per_xcd * N_XCD + b.n_fin + b.n_add)), blk((unsigned)block);
     const size_t lds = record ? 3 * (size_t)V * (size_t)block * sizeof(R) : 0;
     if (record) {
-        if (fields) hipLaunchKernelGGL((k_step3_batch<S, V, true, true>), grid, blk, lds, s, b);
-        else hipLaunchKernelGGL((k_step3_batch<S, V, true, false>), grid, blk, lds, s, b);
+        if (fields) hipLaunchKernelGGL((k_step3_batch<S, V, true, true, OFF32>), grid, blk, lds, s, b);
+        else hipLaunchKernelGGL((k_step3_batch<S, V, true, false, OFF32>), grid, blk, lds, s, b);
     } else {
-        if (fields) hipLaunchKernelGGL((k_step3_batch<S, V, false, true>), grid, blk, 0, s, b);
-        else hipLaunchKernelGGL((k_step3_batch<S, V, false, false>), grid, blk, 0, s, b);
+        if (fields) hipLaunchKernelGGL((k_step3_batch<S, V, false, true, OFF32>), grid, blk, 0, s, b);
+        else hipLaunchKernelGGL((k_step3_batch<S, V, false, false, OFF32>), grid, blk, 0, s, b);
     }
     return hipGetLastError();
+}
+
+template <typename S, int V>
+hipError_t batch_v(bool record, bool fields, const Batch3Launch& b, int32_t block, hipStream_t s)
+{
+    return b.off32 ? batch_off<S, V, true>(record, fields, b, block, s)
+                   : batch_off<S, V, false>(record, fields, b, block, s);
 }
 
 template <typename S>
