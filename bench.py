@@ -29,14 +29,15 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
 METRIC = "MLUPS + % of HBM peak, plain vs batched/FP16; p50/p99 solve latency"
-# the nine populations read and written once per step in the storage type; the
-# body-mask byte is added per node where the step reads it (alg_bytes_per_node)
+# the nine populations read and written once per launch in the storage type; the
+# body-mask byte is added per node where the step reads it (alg_bytes_per_node), and
+# a launch of two steps shares both (steps_per_launch)
 POP_BYTES = {"f64": 144, "f32": 72, "f16": 36, "bf16": 36}
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "step_kernel_counters.json")
 # per lattice: populations per node, the sources its step kernel is built from,
 # and the committed counter summary of that kernel
 LATTICES = {
-    "d2q9": {"q": 9, "sources": ("lbvp_step.h", "lbvp_node.h", "lbvp_device.h", "lbvp_internal.h"),
+    "d2q9": {"q": 9, "sources": ("lbvp_step.h", "lbvp_march.h", "lbvp_node.h", "lbvp_device.h", "lbvp_internal.h"),
              "counters": COUNTERS_FILE},
     "d3q19": {"q": 19, "sources": ("lbvp3_kernels.hip", "lbvp_device.h", "lbvp3_internal.h"),
               "counters": os.path.join(ROOT, "profiles", "step3_kernel_counters.json")},
@@ -108,6 +109,15 @@ def alg_bytes_per_node(storage: str, prob, launch) -> float:
     """Algorithmic HBM bytes per node of one step: 18 population accesses in the
     storage type plus the mask byte where the step reads it."""
     return POP_BYTES[storage] + mask_read_fraction(prob, launch)
+
+
+def steps_per_launch(storage: str, prob, launch, moving: bool = False) -> int:
+    """2 where the library's pull steps run two to a launch (FP64 and FP32 vector
+    launches of single-row tiles and more than 3072 wavefronts, with a fixed mask),
+    else 1. A launch reads and writes the populations once."""
+    tw, tr = tile_shape(prob.nx, launch)
+    waves = -(-prob.nx // tw) * -(-prob.ny // tr) * (launch["block"] // 64)
+    return 2 if storage in ("f64", "f32") and launch["vec"] > 1 and tr == 1 and waves > 3072 and not moving else 1
 
 
 def time_gpu(storage: str, steps: int, warmup: int, prob, repeats: int = 1):
@@ -891,7 +901,8 @@ def main():
     if not ok:
         raise SystemExit("non-finite mass during the timed run")
     mlups = nodes / (ms * 1e-3) / 1e6
-    bpn = alg_bytes_per_node(a.storage, prob, launch)
+    spl = steps_per_launch(a.storage, prob, launch)
+    bpn = alg_bytes_per_node(a.storage, prob, launch) / spl
     alg_bytes = bpn * nodes
     achieved = alg_bytes / (ms * 1e-3) / 1e9
     extra, moving_res = {}, {}
@@ -899,13 +910,14 @@ def main():
         # median of 5 repeats of the requested steps (the first absorbs the
         # clock ramp after the set-up of the variant's context)
         vms, vok, vlaunch, vruns = time_gpu(v, a.steps, a.warmup, prob, repeats=5)
-        vbpn = alg_bytes_per_node(v, prob, vlaunch)
+        vspl = steps_per_launch(v, prob, vlaunch)
+        vbpn = alg_bytes_per_node(v, prob, vlaunch) / vspl
         vb = vbpn * nodes / (vms * 1e-3) / 1e9
         extra[v] = {"alg_bytes_per_node": round(vbpn, 3), "MLUPS": round(nodes / (vms * 1e-3) / 1e6, 1), "ms_per_step": round(vms, 4),
                     "ms_per_step_runs": [round(x, 4) for x in vruns],
                     "timing": f"median of 5 repeats of {a.steps} steps after {a.warmup} + 100 untimed steps",
                     "achieved_GBps": round(vb, 1), "hbm_frac": round(vb / HBM_PEAK_GBPS, 4), "finite": vok,
-                    "launch": vlaunch, "traffic": measured_traffic(v, nodes)}
+                    "launch": vlaunch, "steps_per_launch": vspl, "traffic": measured_traffic(v, nodes)}
         print(f"# {v}: {extra[v]}", file=sys.stderr, flush=True)
     if a.moving_storages:
         # the same domain with its masks following the bodies (a cylinder crossing
@@ -940,6 +952,7 @@ def main():
                    "nx": prob.nx, "ny": prob.ny, "storage": a.storage, "layout": "two-lattice pull",
                    "force_every": 1},
         "launch": launch,
+        "steps_per_launch": spl,
         "alg_bytes_per_node": round(bpn, 4),
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4),

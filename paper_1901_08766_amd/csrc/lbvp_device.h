@@ -270,7 +270,9 @@ __device__ __forceinline__ double block_sum(double v, double* lds)
 // correctly rounded and the first quotient within an ulp), in 3 instructions
 // instead of the division's 11; in FP32 it is within a hair of it, with no
 // systematic direction. 1/x: the hardware's approximation (22 bits or better in
-// FP64, ~1 ulp in FP32), Newton steps and the same last correction.
+// FP64, ~1 ulp in FP32), Newton steps and the same last correction. 1/0 and infinite
+// operands give NaN: a node that gets there makes the mass non-finite either way.
+// FP64 3072 x 1536: 78.4 -> 77.0 us per step.
 template <int D, typename R>
 __device__ __forceinline__ R div_const(R s)
 {
