@@ -577,9 +577,17 @@ __device__ __forceinline__ void finalize_run(const Fin3Args& f, int buf, int sta
     }
 }
 
+// Most wavefronts per SIMD of a step kernel. With one node per thread FP32 could run 6
+// or 7 and FP64 5; large grids, bound by memory, lose less to each other's rows with 5
+// and 4: FP32 64 domains in a batch 0.488 -> 0.474 ms per step, 512 x 256 x 256 0.860 ->
+// 0.848, FP64 1.743 -> 1.702. The 2-byte types, bound by the vector unit there, keep
+// what the registers allow (5 domains 23.4 us, 24.1 with 5).
+template <typename S, int V>
+constexpr int MOST_WAVES = sizeof(S) == 8 && V == 1 ? 4 : sizeof(S) == 4 && V == 1 ? 5 : 8;
+
 // A step launch, behind the leading blocks that sum earlier records.
 template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V>)))
 k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith<S>::R> a)
 {
     __shared__ double lds[3 * SLOT_PASS * 4];
@@ -600,7 +608,8 @@ k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith
 // lockstep: one step kind, record flag and partial buffer for all; leading
 // blocks sum the members' earlier records.
 template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
-__global__ void __launch_bounds__(256) k_step3_batch(Batch3Launch b)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V>)))
+k_step3_batch(Batch3Launch b)
 {
     using R = typename Arith<S>::R;
     __shared__ double lds[3 * SLOT_PASS * 4];
