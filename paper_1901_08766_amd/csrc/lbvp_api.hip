@@ -716,8 +716,8 @@ lbvp_status pose_window(lbvp_ctx* c, int64_t next, int64_t n)
 // vector launches of the pull layout with a fixed mask and no slab cut, tiles that
 // are single rows, room for the partials of four records (place_partials), and
 // more rows of tiles than the chip holds wavefronts of k_march (MARCH_WAVES), so
-// that its chunks have two rows or more. Measured, two steps per launch against
-// one, us per step, recording every step: FP32 8192 x 4096 252 against 385, 3072 x
+// that its chunks have two rows or more. Measured (all stores non-temporal), two
+// steps per launch against one, us per step, recording every step: FP32 8192 x 4096 252 against 385, 3072 x
 // 1536 46.0 against 60.4, 2048 x 1024 24.2 against 29.2; FP64 488 against 782, 78
 // against 115, and 1024 x 1024 25.2 against 28.7. Below the line there is too
 // little to fill the chip: FP32 1024 x 512 12.9 against 9.4. One node per thread
