@@ -31,7 +31,7 @@ HBM_PEAK_GBPS = 8000.0
 METRIC = "MLUPS + % of HBM peak, plain vs batched/FP16; p50/p99 solve latency"
 # the nine populations read and written once per launch in the storage type; the
 # body-mask byte is added per node where the step reads it (alg_bytes_per_node), and
-# a launch of two steps shares both (steps_per_launch)
+# a launch of two steps (Solver.run_info) shares both
 POP_BYTES = {"f64": 144, "f32": 72, "f16": 36, "bf16": 36}
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "step_kernel_counters.json")
 # per lattice: populations per node, the sources its step kernel is built from,
@@ -111,15 +111,6 @@ def alg_bytes_per_node(storage: str, prob, launch) -> float:
     return POP_BYTES[storage] + mask_read_fraction(prob, launch)
 
 
-def steps_per_launch(storage: str, prob, launch, moving: bool = False) -> int:
-    """2 where the library's pull steps run two to a launch (FP64 and FP32 vector
-    launches of single-row tiles and more than 3072 wavefronts, with a fixed mask),
-    else 1. A launch reads and writes the populations once."""
-    tw, tr = tile_shape(prob.nx, launch)
-    waves = -(-prob.nx // tw) * -(-prob.ny // tr) * (launch["block"] // 64)
-    return 2 if storage in ("f64", "f32") and launch["vec"] > 1 and tr == 1 and waves > 3072 and not moving else 1
-
-
 def time_gpu(storage: str, steps: int, warmup: int, prob, repeats: int = 1):
     """ms per step of `steps` steps after `warmup` untimed ones (HIP events on the
     solver's stream); with repeats > 1 the timed run is repeated and the median
@@ -152,7 +143,8 @@ def time_gpu(storage: str, steps: int, warmup: int, prob, repeats: int = 1):
         runs.append(start.elapsed_time(stop) / steps)
         forces, mass, _ = solver.forces()
         ok = ok and bool((mass == mass).all()) and len(mass) == steps
-    launch = {"vec": solver.launch[0], "block": solver.launch[1], "tile_band": solver.tile_band}
+    launch = {"vec": solver.launch[0], "block": solver.launch[1], "tile_band": solver.tile_band,
+              "steps_per_launch": solver.run_info[0]}
     solver.close()
     torch.cuda.empty_cache()
     if repeats == 1:
@@ -901,7 +893,7 @@ def main():
     if not ok:
         raise SystemExit("non-finite mass during the timed run")
     mlups = nodes / (ms * 1e-3) / 1e6
-    spl = steps_per_launch(a.storage, prob, launch)
+    spl = launch.pop("steps_per_launch")
     bpn = alg_bytes_per_node(a.storage, prob, launch) / spl
     alg_bytes = bpn * nodes
     achieved = alg_bytes / (ms * 1e-3) / 1e9
@@ -910,7 +902,7 @@ def main():
         # median of 5 repeats of the requested steps (the first absorbs the
         # clock ramp after the set-up of the variant's context)
         vms, vok, vlaunch, vruns = time_gpu(v, a.steps, a.warmup, prob, repeats=5)
-        vspl = steps_per_launch(v, prob, vlaunch)
+        vspl = vlaunch.pop("steps_per_launch")
         vbpn = alg_bytes_per_node(v, prob, vlaunch) / vspl
         vb = vbpn * nodes / (vms * 1e-3) / 1e9
         extra[v] = {"alg_bytes_per_node": round(vbpn, 3), "MLUPS": round(nodes / (vms * 1e-3) / 1e6, 1), "ms_per_step": round(vms, 4),
@@ -925,12 +917,13 @@ def main():
         mprob = inputs.large_domain(moving=True)
         for v in [s for s in a.moving_storages.split(",") if s]:
             vms, vok, vlaunch, vruns = time_gpu(v, a.steps, a.warmup, mprob, repeats=5)
-            vbpn = alg_bytes_per_node(v, mprob, vlaunch)
+            vspl = vlaunch.pop("steps_per_launch")
+            vbpn = alg_bytes_per_node(v, mprob, vlaunch) / vspl
             vb = vbpn * nodes / (vms * 1e-3) / 1e9
             fixed = ms if v == a.storage else extra.get(v, {}).get("ms_per_step")
             moving_res[v] = {"alg_bytes_per_node": round(vbpn, 3), "MLUPS": round(nodes / (vms * 1e-3) / 1e6, 1), "ms_per_step": round(vms, 4),
                              "ms_per_step_runs": [round(x, 4) for x in vruns], "finite": vok, "launch": vlaunch,
-                             "achieved_GBps": round(vb, 1), "hbm_frac": round(vb / HBM_PEAK_GBPS, 4),
+                             "steps_per_launch": vspl, "achieved_GBps": round(vb, 1), "hbm_frac": round(vb / HBM_PEAK_GBPS, 4),
                              "time_vs_fixed_mask": round(vms / fixed, 4) if fixed else None}
             print(f"# moving {v}: {moving_res[v]}", file=sys.stderr, flush=True)
     traffic = measured_traffic(a.storage, nodes)

@@ -258,6 +258,15 @@ lbvp_status lbvp_get_launch(const lbvp_ctx* ctx, int32_t* vec, int32_t* block);
 lbvp_status lbvp_set_tile_band(lbvp_ctx* ctx, int32_t band);
 lbvp_status lbvp_get_tile_band(const lbvp_ctx* ctx, int32_t* band);
 
+/* How the context's coming lbvp_step calls run (each pointer may be NULL):
+ *   steps_per_launch  2 where two time steps share a launch (the step that keeps the
+ *                     fields and an odd last one run alone), else 1
+ *   rows              rows of the chunk a workgroup of such a launch takes, else 0
+ *   graphs            LBVP_GRAPH runs captured since lbvp_create (a run that
+ *                     replays a kept graph adds none)
+ * Nothing but the order of work depends on it. E_ARG if ctx is NULL. */
+lbvp_status lbvp_get_run_info(const lbvp_ctx* ctx, int32_t* steps_per_launch, int32_t* rows, int64_t* graphs);
+
 /* ---- Batches: many contexts advanced by one launch per step -------------------
  * A batch holds contexts of one storage type and layout on one stream. Each step
  * of lbvp_batch_step is a single launch over the tiles of every member (block ->

@@ -1804,6 +1804,16 @@ lbvp_status lbvp_get_launch(const lbvp_ctx* c, int32_t* vec, int32_t* block)
     return LBVP_OK;
 }
 
+lbvp_status lbvp_get_run_info(const lbvp_ctx* c, int32_t* steps_per_launch, int32_t* rows, int64_t* graphs)
+{
+    if (!c) return LBVP_E_ARG;
+    const bool march = can_march(c);
+    if (steps_per_launch) *steps_per_launch = march ? 2 : 1;
+    if (rows) *rows = march ? march_args(c).rows : 0;
+    if (graphs) *graphs = c->graphs.captured();
+    return LBVP_OK;
+}
+
 lbvp_status lbvp_set_tile_band(lbvp_ctx* c, int32_t band)
 {
     if (check_ctx(c)) return LBVP_E_ARG;

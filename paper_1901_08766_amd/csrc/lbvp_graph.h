@@ -53,6 +53,7 @@ class GraphCache {
             e_.erase(e_.begin());
         }
         e_.emplace_back(k, x);
+        ++captured_;
     }
     void clear(hipStream_t s)
     {
@@ -61,6 +62,7 @@ class GraphCache {
         drop();
     }
     bool empty() const { return e_.empty(); }
+    int64_t captured() const { return captured_; }   // graphs put in so far
 
   private:
     void drop()
@@ -70,6 +72,7 @@ class GraphCache {
     }
     static constexpr size_t CAP = 8;
     std::vector<std::pair<GraphKey, hipGraphExec_t>> e_;
+    int64_t captured_ = 0;
 };
 
 }  // namespace lbvp_host

@@ -44,7 +44,7 @@ SYMBOLS = ["lbvp_footprint_bytes", "lbvp_create", "lbvp_set_mask", "lbvp_init_eq
            "lbvp_pool_forces", "lbvp_pool_read_fields", "lbvp_pool_release", "lbvp_pool_get_stats",
            "lbvp_pool_destroy", "lbvp_pool_last_error", "lbvp_save_state", "lbvp_load_state",
            "lbvp_device_copy", "lbvp_halo_exchange", "lbvp_batch_set_halo", "lbvp_batch_set_tile_band",
-           "lbvp_batch_get_tile_band", "lbvp_batch_step_static"]
+           "lbvp_batch_get_tile_band", "lbvp_batch_step_static", "lbvp_get_run_info"]
 NO_STATUS = ("lbvp_footprint_bytes", "lbvp_step_count", "lbvp_last_error", "lbvp_batch_last_error",
              "lbvp_tune_last_error", "lbvp_pool_last_error")
 
@@ -109,6 +109,7 @@ def _load():
     L.lbvp_write_populations.argtypes = [vp, vp]
     L.lbvp_set_launch.argtypes = [vp, i32, i32]
     L.lbvp_get_launch.argtypes = [vp, C.POINTER(i32), C.POINTER(i32)]
+    L.lbvp_get_run_info.argtypes = [vp, C.POINTER(i32), C.POINTER(i32), C.POINTER(i64)]
     L.lbvp_set_tile_band.argtypes = [vp, i32]
     L.lbvp_get_tile_band.argtypes = [vp, C.POINTER(i32)]
     L.lbvp_step_count.restype = i64
@@ -287,6 +288,13 @@ def lbvp_get_launch(ctx) -> Tuple[int, int]:
     v, b = C.c_int32(), C.c_int32()
     _check(ctx, _L.lbvp_get_launch(ctx, C.byref(v), C.byref(b)))
     return v.value, b.value
+
+
+def lbvp_get_run_info(ctx) -> Tuple[int, int, int]:
+    """(steps per launch, rows of a workgroup's chunk, graphs captured so far)."""
+    n, rows, graphs = C.c_int32(), C.c_int32(), C.c_int64()
+    _check(ctx, _L.lbvp_get_run_info(ctx, C.byref(n), C.byref(rows), C.byref(graphs)))
+    return n.value, rows.value, graphs.value
 
 
 def lbvp_set_tile_band(ctx, band: int):
@@ -560,6 +568,10 @@ class Solver:
 
     def set_launch(self, vec: int, block: int):
         lbvp_set_launch(self.ctx, vec, block)
+
+    @property
+    def run_info(self) -> Tuple[int, int, int]:
+        return lbvp_get_run_info(self.ctx)
 
     @property
     def tile_band(self) -> int:
