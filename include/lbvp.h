@@ -100,7 +100,7 @@ typedef enum lbvp_storage {
 /* lbvp_step / lbvp_batch_step flags
  * LBVP_KEEP_FIELDS: store rho, u, F_VP of the last step of the call.
  * LBVP_GRAPH: enqueue the call through HIP graphs: each run of up to 512 steps is
- * captured once per distinct launch sequence (at most 8 kept per context or
+ * captured once per distinct launch sequence (at most 16 kept per context, 8 per
  * batch) and replayed, which removes the per-launch host cost. Results are
  * bitwise those of the plain call. Needs a stream other than the null stream. */
 #define LBVP_KEEP_FIELDS 0x1u

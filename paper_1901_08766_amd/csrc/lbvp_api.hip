@@ -325,7 +325,9 @@ struct lbvp_ctx {
     std::vector<double> pose_host;          // moving bodies: the uploaded pose table
     int64_t pose_first = -1;                // its first time level (-1: none)
     uint64_t gen = 0;                       // kernel-argument generation (graph keys)
-    GraphCache graphs;
+    // Twice the graphs of a batch: where two steps share a launch, a run of n steps has
+    // both lattice parities at every record phase, which single steps have for odd n only.
+    GraphCache graphs{16};
     StepArgs<double> a64{};
     StepArgs<float> a32{};
     FinalizeArgs fin{};
@@ -479,10 +481,33 @@ std::vector<char> body_table_bytes(const lbvp_body* bodies, int32_t n, int32_t m
     return out;
 }
 
+// Whether the context's launch shape is one whose steps run two to a launch
+// (k_march): FP64 or FP32 vector launches of the pull layout with a fixed mask and no
+// slab cut, tiles that are single rows, and more rows of tiles than the chip holds
+// wavefronts of k_march (MARCH_WAVES), so that its chunks have two rows or more. Measured (all stores non-temporal), two
+// steps per launch against one, us per step, recording every step: FP32 8192 x 4096 252 against 385, 3072 x
+// 1536 46.0 against 60.4, 2048 x 1024 24.2 against 29.2; FP64 488 against 782, 78
+// against 115, and 1024 x 1024 25.2 against 28.7. Below the line there is too
+// little to fill the chip: FP32 1024 x 512 12.9 against 9.4. One node per thread
+// loses everywhere (1024 x 512 11.5 against 9.1), and 2-byte storage is bound by its
+// conversions and arithmetic: FP16 8192 x 4096 195 against 203, but BF16 2305 x 1153
+// 30 against 23. An offset within a row has to fit 31 bits.
+bool march_shape(const lbvp_ctx* c)
+{
+    const Launch& l = c->launch;
+    return (c->p.storage == LBVP_F64 || c->p.storage == LBVP_F32) && l.vec > 1 && !c->aa() && !c->moving() &&
+           c->p.bc_west != LBVP_BC_NEIGHBOR && c->p.bc_east != LBVP_BC_NEIGHBOR && l.tile_rows == 1 &&
+           c->L.lstride * (int64_t)c->esize() < (int64_t(1) << 30) &&
+           (int64_t)l.n_tiles * (l.block / 64) > MARCH_WAVES;
+}
+
+// ... and whether they do: there is room for the partials of four records.
+bool can_march(const lbvp_ctx* c) { return c->fin.n_buf == 4 && march_shape(c); }
+
 // Where the record partials of the current tiling live and how many buffers they
-// have: four if they fit the tables' areas (vector launches need a fraction of
-// them, which are sized for the finest tiling) or the staging area (which only
-// conversions between runs use), else two.
+// have: two, or four where two steps can share a launch and they fit the tables'
+// areas (vector launches need a fraction of them, which are sized for the finest
+// tiling) or the staging area (which only conversions between runs use).
 void place_partials(lbvp_ctx* c, size_t n_slots)
 {
     const Layout& L = c->L;
@@ -492,7 +517,7 @@ void place_partials(lbvp_ctx* c, size_t n_slots)
     c->fin.mass_stride = L.max_waves;
     c->fin.slot_stride = L.slot_cap * 2;
     c->fin.n_buf = 2;
-    if (c->moving()) return;   // their slots change between runs
+    if (!march_shape(c)) return;
     if (4 * n_mass <= 2 * (int64_t)L.max_waves && 4 * n_force <= 4 * L.slot_cap) {
         c->fin.mass_stride = n_mass;
         c->fin.slot_stride = n_force;
@@ -712,27 +737,6 @@ lbvp_status pose_window(lbvp_ctx* c, int64_t next, int64_t n)
     return st;
 }
 
-// Whether the context's coming steps run two to a launch (k_march): FP64 or FP32
-// vector launches of the pull layout with a fixed mask and no slab cut, tiles that
-// are single rows, room for the partials of four records (place_partials), and
-// more rows of tiles than the chip holds wavefronts of k_march (MARCH_WAVES), so
-// that its chunks have two rows or more. Measured (all stores non-temporal), two
-// steps per launch against one, us per step, recording every step: FP32 8192 x 4096 252 against 385, 3072 x
-// 1536 46.0 against 60.4, 2048 x 1024 24.2 against 29.2; FP64 488 against 782, 78
-// against 115, and 1024 x 1024 25.2 against 28.7. Below the line there is too
-// little to fill the chip: FP32 1024 x 512 12.9 against 9.4. One node per thread
-// loses everywhere (1024 x 512 11.5 against 9.1), and 2-byte storage is bound by its
-// conversions and arithmetic: FP16 8192 x 4096 195 against 203, but BF16 2305 x 1153
-// 30 against 23. An offset within a row has to fit 31 bits.
-bool can_march(const lbvp_ctx* c)
-{
-    const Launch& l = c->launch;
-    return (c->p.storage == LBVP_F64 || c->p.storage == LBVP_F32) && l.vec > 1 && !c->aa() && !c->moving() &&
-           c->p.bc_west != LBVP_BC_NEIGHBOR && c->p.bc_east != LBVP_BC_NEIGHBOR && l.tile_rows == 1 &&
-           c->fin.n_buf == 4 && c->L.lstride * (int64_t)c->esize() < (int64_t(1) << 30) &&
-           (int64_t)l.n_tiles * (l.block / 64) > MARCH_WAVES;
-}
-
 // The chunks of a two-step launch: as few rows as still let the chip hold all
 // workgroups at once, up to 6, for a chunk of H rows does H + 2 rows of the first
 // step. Above 6 the rows a workgroup takes one after the other cost more than the
@@ -763,11 +767,14 @@ lbvp_status enqueue_steps(lbvp_ctx* c, int64_t n_steps, bool keep_last, bool lau
     MarchArgs m{};
     if (march) m = march_args(c);
     const void* args = c->is_f64() ? (const void*)&c->a64 : (const void*)&c->a32;
+    // A run starts with partial buffer 0, for the run before left nothing to sum:
+    // the launches then depend on the steps alone, not on the records so far.
+    int32_t part_buf = c->pending ? c->pending_buf + c->pending : 0;
     for (int64_t k = 0; k < n_steps;) {
         // the step that keeps the fields runs alone
         const int64_t n = march && n_steps - k >= (keep_last ? 3 : 2) ? 2 : 1;
         const bool keep = keep_last && k + n == n_steps;
-        const int32_t part_buf = (int32_t)(c->rec_head & (c->fin.n_buf - 1));
+        part_buf &= c->fin.n_buf - 1;
         const bool rec0 = fe > 0 && (c->step + 1) % fe == 0, rec1 = n == 2 && fe > 0 && (c->step + 2) % fe == 0;
         if (launch) {
             c->a64.part_buf = c->a32.part_buf = part_buf;
@@ -791,6 +798,7 @@ lbvp_status enqueue_steps(lbvp_ctx* c, int64_t n_steps, bool keep_last, bool lau
         c->pending = (rec0 ? 1 : 0) + (rec1 ? 1 : 0);
         if (c->pending) {
             c->pending_buf = part_buf;
+            part_buf += c->pending;
             c->rec_head += c->pending;
         }
         if (keep) c->fields_valid = true;
@@ -1500,7 +1508,6 @@ lbvp_status lbvp_step(lbvp_ctx* c, int64_t n_steps, uint32_t flags)
         key.cur = c->cur;
         key.par = c->aa() ? (int32_t)(c->step & 1) : 0;
         key.phase = fe > 0 ? c->step % fe : 0;
-        key.rec = (int32_t)(c->rec_head & (c->fin.n_buf - 1));
         key.gen = c->gen;
         hipGraphExec_t x = c->graphs.find(key);
         if (x) {

@@ -29,7 +29,7 @@ struct GraphKey {
 // A few instantiated graphs, most recently used last.
 class GraphCache {
   public:
-    GraphCache() = default;
+    explicit GraphCache(size_t cap = 8) : cap_(cap) {}
     GraphCache(const GraphCache&) = delete;
     GraphCache& operator=(const GraphCache&) = delete;
     ~GraphCache() { drop(); }
@@ -47,7 +47,7 @@ class GraphCache {
     // An evicted graph may still run: the stream is drained before it is freed.
     void put(const GraphKey& k, hipGraphExec_t x, hipStream_t s)
     {
-        if (e_.size() == CAP) {
+        if (e_.size() == cap_) {
             (void)hipStreamSynchronize(s);
             (void)hipGraphExecDestroy(e_.front().second);
             e_.erase(e_.begin());
@@ -70,7 +70,7 @@ class GraphCache {
         for (auto& x : e_) (void)hipGraphExecDestroy(x.second);
         e_.clear();
     }
-    static constexpr size_t CAP = 8;
+    const size_t cap_;
     std::vector<std::pair<GraphKey, hipGraphExec_t>> e_;
     int64_t captured_ = 0;
 };
