@@ -89,10 +89,14 @@ Staging g_idle[KEPT];
 int g_n_idle = 0;
 int64_t g_users = 0;
 
-hipError_t acquire(Staging* out)
+// Buffers for work on s: its events have to be of the stream's device, which need
+// not be the calling thread's current one (it stays as it was).
+hipError_t acquire(hipStream_t s, Staging* out)
 {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
+    int current = 0;
+    hipError_t e = hipGetDevice(&current);
+    int dev = current;   // the null stream's
+    if (e == hipSuccess && s) e = hipStreamGetDevice(s, &dev);
     if (e != hipSuccess) return e;
     {
         std::lock_guard<std::mutex> lock(g_mu);
@@ -103,19 +107,21 @@ hipError_t acquire(Staging* out)
                 return hipSuccess;
             }
     }
-    Staging s;
-    s.dev = dev;
+    Staging st;
+    st.dev = dev;
+    if (dev != current) e = hipSetDevice(dev);
     for (int i = 0; i < 2 && e == hipSuccess; ++i) {
         void* m = nullptr;
         e = hipHostMalloc(&m, CHUNK_BYTES, hipHostMallocDefault);
-        s.p[i] = static_cast<char*>(m);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&s.ev[i], hipEventDisableTiming);
+        st.p[i] = static_cast<char*>(m);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&st.ev[i], hipEventDisableTiming);
     }
+    if (dev != current) (void)hipSetDevice(current);
     if (e != hipSuccess) {
-        destroy(s);
+        destroy(st);
         return e;
     }
-    *out = s;
+    *out = st;
     return hipSuccess;
 }
 
@@ -182,7 +188,7 @@ hipError_t read_planes(hipStream_t s, bool is_f64, const void* base, const int64
     a.nx = (uint32_t)nx;
     a.per_plane = (uint64_t)nx * (uint64_t)rows;
     Staging st;
-    hipError_t e = acquire(&st);
+    hipError_t e = acquire(s, &st);
     if (e != hipSuccess) return e;
     e = is_f64 ? read_typed<double>(s, a, n, dst, st) : read_typed<float>(s, a, n, dst, st);
     if (e != hipSuccess) (void)hipStreamSynchronize(s);   // nothing may still write the buffers
@@ -195,7 +201,7 @@ hipError_t write_mask(hipStream_t s, uint8_t* dst, int64_t pitch, int32_t nx, in
     if (nx < 1 || rows < 0) return hipErrorInvalidValue;
     if (rows == 0) return hipSuccess;
     Staging st;
-    hipError_t e = acquire(&st);
+    hipError_t e = acquire(s, &st);
     if (e != hipSuccess) return e;
     const uint64_t total = (uint64_t)nx * (uint64_t)rows;
     bool used[2] = {false, false};
