@@ -16,7 +16,9 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
+#include <new>
 
 #include "lbvp_readback.h"
 
@@ -174,6 +176,29 @@ hipError_t read_typed(hipStream_t s, PackArgs a, int n, double* const* dst, Stag
     return e;
 }
 
+// Where no staging buffers can be had, the pitched copies of the runtime: to
+// pageable memory, a share of a plane's rows at a time.
+template <typename R>
+hipError_t read_pageable(hipStream_t s, const PackArgs& a, int n, double* const* dst)
+{
+    const size_t row = (size_t)a.nx * sizeof(R);
+    const uint64_t rows = a.per_plane / a.nx, share = std::min<uint64_t>(rows, std::max<uint64_t>(1, CHUNK_BYTES / row));
+    const std::unique_ptr<R[]> tmp(new (std::nothrow) R[share * a.nx]);
+    if (!tmp) return hipErrorOutOfMemory;
+    for (int q = 0; q < n; ++q)
+        for (uint64_t r = 0; r < rows; r += share) {
+            const uint64_t k = std::min(share, rows - r);
+            const R* from = static_cast<const R*>(a.base) + a.off[q] + (int64_t)r * a.pitch;
+            hipError_t e = hipMemcpy2DAsync(tmp.get(), row, from, (size_t)a.pitch * sizeof(R), row, (size_t)k,
+                                            hipMemcpyDeviceToHost, s);
+            const hipError_t w = hipStreamSynchronize(s);
+            if (e == hipSuccess) e = w;
+            if (e != hipSuccess) return e;
+            widen(dst[q] + r * a.nx, tmp.get(), (size_t)(k * a.nx));
+        }
+    return hipSuccess;
+}
+
 }  // namespace
 
 hipError_t read_planes(hipStream_t s, bool is_f64, const void* base, const int64_t* off, int n, int64_t pitch,
@@ -189,7 +214,10 @@ hipError_t read_planes(hipStream_t s, bool is_f64, const void* base, const int64
     a.per_plane = (uint64_t)nx * (uint64_t)rows;
     Staging st;
     hipError_t e = acquire(s, &st);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return is_f64 ? read_pageable<double>(s, a, n, dst) : read_pageable<float>(s, a, n, dst);
+    }
     e = is_f64 ? read_typed<double>(s, a, n, dst, st) : read_typed<float>(s, a, n, dst, st);
     if (e != hipSuccess) (void)hipStreamSynchronize(s);   // nothing may still write the buffers
     put_back(st);
@@ -202,7 +230,12 @@ hipError_t write_mask(hipStream_t s, uint8_t* dst, int64_t pitch, int32_t nx, in
     if (rows == 0) return hipSuccess;
     Staging st;
     hipError_t e = acquire(s, &st);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        e = hipMemcpy2DAsync(dst, (size_t)pitch, src, (size_t)nx, (size_t)nx, (size_t)rows, hipMemcpyHostToDevice, s);
+        const hipError_t w = hipStreamSynchronize(s);
+        return e != hipSuccess ? e : w;
+    }
     const uint64_t total = (uint64_t)nx * (uint64_t)rows;
     bool used[2] = {false, false};
     for (uint64_t at = 0, k = 0; at < total && e == hipSuccess; at += CHUNK_BYTES, ++k) {

@@ -19,6 +19,7 @@ struct ihipEvent_t {
 };
 
 namespace fake {
+bool no_pinned = false;   // pinned host memory is used up
 int current = 0, launches = 0, host_allocs = 0, host_frees = 0, events = 0, copies = 0;
 hipError_t last = hipSuccess;
 hipError_t note(hipError_t e)
@@ -65,6 +66,7 @@ hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d)
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipHostMalloc(void** p, size_t n, unsigned)
 {
+    if (fake::no_pinned) return fake::note(hipErrorOutOfMemory);
     *p = std::malloc(n);
     fake::host_allocs += 1;
     return hipSuccess;
@@ -147,10 +149,39 @@ static int devices()
     return 0;
 }
 
+// Without pinned memory the calls copy through pageable memory, leave no error behind,
+// and use staging again when there is some.
+static int pageable()
+{
+    ihipStream_t s{0};
+    std::vector<float> dev(2 * (size_t)ROWS * PITCH);
+    for (size_t k = 0; k < dev.size(); ++k) dev[k] = (float)(k % 8191);
+    std::vector<uint8_t> mask((size_t)NX * ROWS), dmask((size_t)PITCH * ROWS, 255);
+    for (size_t k = 0; k < mask.size(); ++k) mask[k] = (uint8_t)(k % 251);
+    std::vector<double> out;
+    lbvp::ReadbackUser user;
+    fake::no_pinned = true;
+    CHECK(lbvp::write_mask(&s, dmask.data(), PITCH, NX, ROWS, mask.data()) == hipSuccess);
+    CHECK(read_some(&s, dev, out) == hipSuccess);
+    CHECK(hipGetLastError() == hipSuccess);
+    CHECK(fake::launches == 0 && fake::host_allocs == fake::host_frees);
+    for (int r = 0; r < ROWS; ++r)
+        for (int i = 0; i < PITCH; ++i) {
+            CHECK(dmask[(size_t)r * PITCH + i] == (i < NX ? mask[(size_t)r * NX + i] : 255));
+            for (int q = 0; q < 2 && i < NX; ++q)
+                CHECK(out[((size_t)q * ROWS + r) * NX + i] == dev[((size_t)q * ROWS + r) * PITCH + i]);
+        }
+    fake::no_pinned = false;
+    CHECK(read_some(&s, dev, out) == hipSuccess);
+    CHECK(fake::launches > 0);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "devices")) return devices();
+    if (!std::strcmp(what, "pageable")) return pageable();
     std::printf("unknown check %s\n", what);
     return 2;
 }
