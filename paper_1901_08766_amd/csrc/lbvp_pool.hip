@@ -14,6 +14,7 @@
 
 #include "lbvp.h"
 #include "lbvp_internal.h"
+#include "lbvp_readback.h"
 
 using namespace lbvp;
 
@@ -129,6 +130,7 @@ thread_local std::string g_pool_error;
 }  // namespace
 
 struct lbvp_pool {
+    ReadbackUser readback;           // the staging buffers stay between solves
     lbvp_pool_config cfg{};
     hipStream_t stream = nullptr;    // borrowed: epochs
     hipStream_t admin = nullptr;     // owned: set-up and result copies

@@ -22,7 +22,7 @@ hipError_t read_planes(hipStream_t s, bool is_f64, const void* base, const int64
 hipError_t write_mask(hipStream_t s, uint8_t* dst, int64_t pitch, int32_t nx, int64_t rows, const uint8_t* src);
 
 // The pinned staging buffers that both use are kept between calls while
-// any context lives: every context counts itself in and out.
+// any context or pool lives: each counts itself in and out.
 void readback_retain();
 void readback_release();
 struct ReadbackUser {

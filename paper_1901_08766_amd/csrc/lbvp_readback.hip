@@ -84,7 +84,7 @@ void destroy(Staging& s)
     s = Staging{};
 }
 
-// Idle buffers: at most KEPT pairs (16 MiB), none once the last context is gone.
+// Idle buffers: at most KEPT pairs (16 MiB), none once the last user is gone.
 constexpr int KEPT = 4;
 std::mutex g_mu;
 Staging g_idle[KEPT];
