@@ -5,6 +5,8 @@
 #include "lbvp.h"
 #include "lbvp_internal.h"
 
+#include <array>
+
 namespace lbvp {
 int vector_width(int32_t storage) { return storage == ST_F64 ? 2 : storage == ST_F32 ? 4 : 8; }
 int32_t batch_fin_share(int32_t) { return 1; }
@@ -75,10 +77,32 @@ static int pool_staging()
     return 0;
 }
 
+// Members whose tables fill the 4 MiB array of lbvp_batch_step_static: as many as ever
+// fit (648 bytes of arguments a member in FP64, 536 in FP32, a tile and its start), and
+// no more.
+static int static_capacity()
+{
+    ihipStream_t s{0};
+    for (const auto& [storage, fit, refused] : {std::array<int, 3>{LBVP_F64, 6390, 6400}, {LBVP_F32, 7700, 7720}}) {
+        const lbvp_params p = params(3, 3, storage);
+        const size_t n = lbvp_footprint_bytes(&p);
+        void* mem = nullptr;
+        CHECK(hipMalloc(&mem, n) == hipSuccess);
+        std::vector<lbvp_ctx*> c((size_t)refused, nullptr);
+        for (lbvp_ctx*& x : c) CHECK(lbvp_create(&p, &s, mem, n, &x) == LBVP_OK);   // nothing runs: one memory for all
+        CHECK(lbvp_batch_step_static(c.data(), fit, 1, 0) == LBVP_OK);
+        CHECK(lbvp_batch_step_static(c.data(), refused, 1, 0) == LBVP_E_ARG);
+        for (lbvp_ctx* x : c) CHECK(lbvp_destroy(x) == LBVP_OK);
+        hipFree(mem);
+    }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "pool_staging")) return pool_staging();
+    if (!std::strcmp(what, "static_capacity")) return static_capacity();
     std::printf("unknown check %s\n", what);
     return 2;
 }
