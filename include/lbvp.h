@@ -237,9 +237,14 @@ lbvp_status lbvp_load_state(lbvp_ctx* ctx, const void* buf, size_t size);
  * on it; the force and mass records do only through the per-tile partial sums
  * (each record is then summed in an order fixed by the data, independent of the
  * block size and of how steps are split over calls). A default is chosen from
- * the grid size at lbvp_create; lbvp_tune measures the others. Errors: E_ARG
- * (other values), E_STATE (undrained force records when the shape changes).
- * Synchronizes the stream when the shape changes. */
+ * the grid size at lbvp_create; lbvp_tune measures the others. A default with
+ * blocks below the 256 threads of similar grids (ragged rows, 2-byte storage) that
+ * was not set again becomes (vec, 256) where that is needed: for a mask with more
+ * (tile, body) pairs than its smaller tiles can list, and in
+ * lbvp_batch_step_static next to members of that shape. Errors: E_ARG
+ * (other values), E_STATE (undrained force records when the shape changes, unless
+ * from such a default to (vec, 256)). Synchronizes the stream when the shape
+ * changes. */
 lbvp_status lbvp_set_launch(lbvp_ctx* ctx, int32_t vec, int32_t block);
 lbvp_status lbvp_get_launch(const lbvp_ctx* ctx, int32_t* vec, int32_t* block);
 

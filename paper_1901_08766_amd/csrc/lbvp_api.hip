@@ -131,7 +131,8 @@ bool vec_allowed(int32_t storage, uint32_t flags, int32_t vec)
 // FP64 128 threads, bands of 2 (0.789-0.792 against 0.812); FP16 and BF16 256
 // threads of 4 nodes (8-byte accesses), bands of 16 (FP16 0.208 ms, BF16 0.209,
 // against 0.210 and 0.213 for 8 nodes in bands of 2 and 0.221 for 128 threads).
-Launch default_launch(int32_t nx, int32_t ny, int32_t storage, uint32_t flags)
+// *narrowed: the blocks are smaller than the MAX_BLOCK that other grids of the size take.
+Launch default_launch(int32_t nx, int32_t ny, int32_t storage, uint32_t flags, bool* narrowed)
 {
     const int64_t n = (int64_t)nx * ny;
     const bool two_byte = storage == LBVP_F16_DEV || storage == LBVP_BF16_DEV;
@@ -155,6 +156,7 @@ Launch default_launch(int32_t nx, int32_t ny, int32_t storage, uint32_t flags)
         const Launch s = make_launch(nx, ny, vec, b);
         if ((int64_t)s.tiles_x * s.tile_w * 16 < (int64_t)l.tiles_x * l.tile_w * 15) l = s;
     }
+    *narrowed = l.block < block;
     if (vec > 1 && !(flags & LBVP_LAYOUT_AA)) l.band = storage == LBVP_F32 ? 8 : (two_byte && vec == 4) ? 16 : 2;
     return l;
 }
@@ -316,6 +318,7 @@ struct lbvp_ctx {
     int32_t n_bodies = 0;
     double tau_minus = 0.0;
     Launch launch;
+    bool narrowed = false;                  // by default_launch, from MAX_BLOCK threads (widen)
     std::vector<uint8_t> mask_host;         // [ny][nx], kept to rebuild the tile tables
     std::vector<lbvp_body> bodies_host;
     std::vector<double> mov_r2;             // moving bodies: squared reach about the centre
@@ -531,6 +534,8 @@ void place_partials(lbvp_ctx* c, size_t n_slots)
     }
 }
 
+lbvp_status widen(lbvp_ctx* c);
+
 // The (tile, body) reduction tables for the current tiling and mask: a slot per
 // body present in each tile, numbered in tile order, and each body's slots.
 // Moving bodies: with a pose window on the device (time levels pose_first ..
@@ -609,6 +614,7 @@ lbvp_status build_tile_tables(lbvp_ctx* c)
             if (!seen[b]) continue;
             if ((int64_t)slot_body.size() >= L.slot_cap) {
                 (void)hipStreamSynchronize(c->stream);  // copies from the caller's host buffers
+                if (c->narrowed) return widen(c);       // fewer tiles, fewer pairs
                 return c->fail(LBVP_E_NOMEM, "mask has more (tile, body) pairs than the reduction tables hold");
             }
             per_body[b - 1].push_back((int32_t)slot_body.size());
@@ -650,6 +656,19 @@ lbvp_status apply_launch(lbvp_ctx* c, const Launch& l)
     fill_step_args(c, c->a64);
     fill_step_args(c, c->a32);
     return build_tile_tables(c);
+}
+
+// A default shape with smaller blocks than MAX_BLOCK gives way to MAX_BLOCK, the default
+// of the unragged grids of its size, where a context of theirs would be taken: undrained
+// records do not stand against it, for every run has summed its own.
+lbvp_status widen(lbvp_ctx* c)
+{
+    LBVP_HIP(c, hipStreamSynchronize(c->stream));
+    c->graphs.clear(c->stream);
+    Launch l = make_launch(c->p.nx, c->p.ny, c->launch.vec, MAX_BLOCK);
+    l.band = c->launch.band;
+    c->narrowed = false;
+    return apply_launch(c, l);
 }
 
 ConvArgs conv_args(lbvp_ctx* c, int32_t row0, int32_t rows)
@@ -1337,7 +1356,7 @@ lbvp_status lbvp_create(const lbvp_params* p, void* hip_stream, void* dev_mem, s
         c->mem = static_cast<char*>(m);
         c->owns = true;
     }
-    c->launch = default_launch(p->nx, p->ny, p->storage, p->flags);
+    c->launch = default_launch(p->nx, p->ny, p->storage, p->flags, &c->narrowed);
     c->fin.max_bodies = c->L.max_bodies;
     c->fin.n_mass = c->launch.n_tiles * (c->launch.block / 64);
     c->fin.capacity = c->L.capacity;
@@ -1794,12 +1813,17 @@ lbvp_status lbvp_set_launch(lbvp_ctx* c, int32_t vec, int32_t block)
         return c->fail(LBVP_E_ARG, "vec must be 1, the storage type's 16-byte vector width or, for "
                                    "2-byte storage, 4 (1 only for 2-byte storage in the AA layout)");
     if (block != 64 && block != 128 && block != 256) return c->fail(LBVP_E_ARG, "block must be 64, 128 or 256");
-    if (c->launch.vec == vec && c->launch.block == block) return LBVP_OK;
+    if (c->launch.vec == vec && c->launch.block == block) {
+        c->narrowed = false;   // the caller's choice from now on
+        return LBVP_OK;
+    }
+    if (c->narrowed && c->launch.vec == vec && block == MAX_BLOCK) return widen(c);
     if (c->rec_head != c->rec_tail) return c->fail(LBVP_E_STATE, "drain the force records first");
     LBVP_HIP(c, hipStreamSynchronize(c->stream));
     c->graphs.clear(c->stream);
     Launch l = make_launch(c->p.nx, c->p.ny, vec, block);
     l.band = c->launch.band;
+    c->narrowed = false;
     return apply_launch(c, l);
 }
 
@@ -2024,9 +2048,16 @@ lbvp_status lbvp_batch_step_static(lbvp_ctx* const* members, int32_t n, int64_t 
     for (int32_t i = 0; i < n; ++i)
         if (check_ctx(members[i])) return batch_static_fail(LBVP_E_ARG, "a member is NULL or not a context");
     const lbvp_ctx* c0 = members[0];
-    for (int32_t i = 0; i < n; ++i)
-        if (members[i]->launch.vec != c0->launch.vec || members[i]->launch.block != c0->launch.block)
-            return batch_static_fail(LBVP_E_ARG, "members need the first member's launch shape (lbvp_set_launch)");
+    // one launch shape, the narrowed defaults widened if it takes that
+    bool as_is = true, widened = true;
+    auto wide = [](const lbvp_ctx* c) { return c->narrowed ? MAX_BLOCK : c->launch.block; };
+    for (int32_t i = 0; i < n; ++i) {
+        const lbvp_ctx* c = members[i];
+        as_is = as_is && c->launch.vec == c0->launch.vec && c->launch.block == c0->launch.block;
+        widened = widened && c->launch.vec == c0->launch.vec && wide(c) == wide(c0);
+    }
+    if (!as_is && !widened)
+        return batch_static_fail(LBVP_E_ARG, "members need the first member's launch shape (lbvp_set_launch)");
     // a batch object on the host only: its device block is the static array
     lbvp_batch b;
     b.stream = c0->stream;
@@ -2034,7 +2065,7 @@ lbvp_status lbvp_batch_step_static(lbvp_ctx* const* members, int32_t n, int64_t 
     b.aa = c0->aa();
     b.force_every = c0->p.force_every;
     b.vec = c0->launch.vec;
-    b.block = c0->launch.block;
+    b.block = as_is ? c0->launch.block : wide(c0);
     const std::vector<lbvp_ctx*> m(members, members + n);
     const std::string why = batch_consistency(&b, m);
     if (!why.empty()) return batch_static_fail(LBVP_E_ARG, why);
@@ -2045,6 +2076,12 @@ lbvp_status lbvp_batch_step_static(lbvp_ctx* const* members, int32_t n, int64_t 
     for (lbvp_ctx* c : m)
         if (c->rec_head + new_recs - c->rec_tail > c->L.capacity)
             return batch_static_fail(LBVP_E_STATE, "a member's force ring would overflow; drain it with lbvp_forces first");
+    if (!as_is)
+        for (lbvp_ctx* c : m)
+            if (c->narrowed) {
+                const lbvp_status st = widen(c);
+                if (st != LBVP_OK) return batch_static_fail(st, "a member's launch shape: " + c->err);
+            }
     batch_layout(&b, m);
     if (b.bytes > STATIC_SCRATCH_BYTES) {
         std::ostringstream os;

@@ -98,11 +98,68 @@ static int static_capacity()
     return 0;
 }
 
+// A ragged 2-byte grid whose default shape has smaller blocks than the 256 threads of
+// other grids is still taken wherever a context of 256 would be: next to their defaults
+// in lbvp_batch_step_static, with undrained records where its shape becomes (4, 256), and
+// with as many (tile, body) pairs.
+static int default_shape()
+{
+    ihipStream_t s{0};
+    lbvp_params a = params(2305, 1153, LBVP_F16_DEV), b = params(2048, 1200, LBVP_F16_DEV);
+    a.max_bodies = 20;
+    auto make = [&](const lbvp_params& p) {
+        lbvp_ctx* c = nullptr;
+        return lbvp_create(&p, &s, nullptr, 0, &c) == LBVP_OK ? c : nullptr;
+    };
+    auto is = [](const lbvp_ctx* c, int32_t v, int32_t k) {
+        int32_t vec = 0, block = 0;
+        return lbvp_get_launch(c, &vec, &block) == LBVP_OK && vec == v && block == k;
+    };
+    lbvp_ctx *m[2] = {make(a), make(b)}, *same[2] = {make(a), make(a)}, *later[2] = {m[1], make(a)};
+    CHECK(m[0] && m[1] && same[0] && same[1] && later[1]);
+    CHECK(is(m[0], 4, 128) && is(m[1], 4, 256));
+    CHECK(lbvp_step(m[0], 3, 0) == LBVP_OK);
+    CHECK(lbvp_batch_step_static(m, 2, 1, 0) == LBVP_OK);
+    CHECK(is(m[0], 4, 256) && is(m[1], 4, 256));
+    CHECK(lbvp_step(m[0], 1, 0) == LBVP_OK);
+    CHECK(lbvp_batch_step_static(later, 2, 1, 0) == LBVP_OK);
+    // shapes that agree stay; a set one is not changed, nor is anything by a refused call
+    CHECK(lbvp_batch_step_static(same, 2, 1, 0) == LBVP_OK && is(same[0], 4, 128) && is(same[1], 4, 128));
+    lbvp_ctx *fixed = make(a), *open = make(a), *bad[3] = {m[1], fixed, open};
+    CHECK(fixed && open && lbvp_set_launch(fixed, 4, 128) == LBVP_OK);
+    CHECK(lbvp_batch_step_static(bad, 3, 1, 0) == LBVP_E_ARG);
+    CHECK(is(fixed, 4, 128) && is(open, 4, 128));
+    // undrained records
+    lbvp_ctx *c = make(a), *d = make(a);
+    CHECK(c && lbvp_step(c, 3, 0) == LBVP_OK);
+    CHECK(lbvp_set_launch(c, 4, 64) == LBVP_E_STATE);
+    CHECK(lbvp_set_launch(c, 8, 256) == LBVP_E_STATE);
+    lbvp_batch* batch = nullptr;
+    CHECK(lbvp_batch_create(&c, 1, 4, 256, &batch) == LBVP_OK);
+    CHECK(lbvp_batch_step(batch, 2, 0) == LBVP_OK);
+    CHECK(lbvp_batch_destroy(batch) == LBVP_OK);
+    CHECK(d && lbvp_step(d, 3, 0) == LBVP_OK);
+    CHECK(lbvp_set_launch(d, 4, 256) == LBVP_OK && is(d, 4, 256));
+    CHECK(lbvp_set_launch(d, 4, 128) == LBVP_E_STATE);
+    // 20 bodies in every tile: room for that many pairs in tiles of (4, 256) only
+    std::vector<uint8_t> mask((size_t)a.nx * a.ny);
+    for (size_t k = 0; k < mask.size(); ++k) mask[k] = (uint8_t)(k % a.nx % 20 + 1);
+    const std::vector<lbvp_body> bodies(20, lbvp_body{});
+    lbvp_ctx* e = make(a);
+    CHECK(e && lbvp_set_mask(e, mask.data(), 20, bodies.data()) == LBVP_OK && is(e, 4, 256));
+    CHECK(lbvp_step(e, 3, 0) == LBVP_OK);
+    CHECK(lbvp_set_launch(fixed, 4, 64) == LBVP_OK);
+    CHECK(lbvp_set_mask(fixed, mask.data(), 20, bodies.data()) == LBVP_E_NOMEM);
+    for (lbvp_ctx* x : {m[0], m[1], same[0], same[1], later[1], fixed, open, c, d, e}) CHECK(lbvp_destroy(x) == LBVP_OK);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "pool_staging")) return pool_staging();
     if (!std::strcmp(what, "static_capacity")) return static_capacity();
+    if (!std::strcmp(what, "default_shape")) return default_shape();
     std::printf("unknown check %s\n", what);
     return 2;
 }
