@@ -342,7 +342,7 @@ lbvp_status lbvp_batch_step_static(lbvp_ctx* const* members, int32_t n, int64_t 
  * when layouts are compared, the fastest AA row wins if within 3% of the
  * fastest row, for its halved lattice memory. Results are cached per process,
  * keyed by storage, layout, record cadence, steps and the members' grid sizes,
- * unless LBVP_TUNE_FRESH. Errors (message from lbvp_tune_last_error): E_ARG,
+ * moving bodies and cuts, unless LBVP_TUNE_FRESH. Errors (message from lbvp_tune_last_error): E_ARG,
  * E_NOMEM, E_DEVICE. */
 #define LBVP_TUNE_LAYOUTS 0x1u
 #define LBVP_TUNE_FRESH 0x2u

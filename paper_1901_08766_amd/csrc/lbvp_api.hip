@@ -1208,15 +1208,18 @@ std::map<std::string, std::pair<std::vector<lbvp_tune_row>, int32_t>> g_tune_cac
 
 std::string tune_signature(const std::vector<lbvp_ctx*>& m, int32_t steps, uint32_t flags)
 {
-    // a domain's size and whether it runs the moving-body kernels
-    std::vector<std::array<int32_t, 3>> shapes;
-    for (const lbvp_ctx* c : m) shapes.push_back({c->p.nx, c->p.ny, c->moving() ? c->n_bodies : 0});
+    // a domain's size, whether it runs the moving-body kernels, and whether it has a cut
+    // (which runs single steps where a whole domain may run two a launch)
+    std::vector<std::array<int32_t, 4>> shapes;
+    for (const lbvp_ctx* c : m)
+        shapes.push_back({c->p.nx, c->p.ny, c->moving() ? c->n_bodies : 0,
+                          c->p.bc_west == LBVP_BC_NEIGHBOR || c->p.bc_east == LBVP_BC_NEIGHBOR});
     std::sort(shapes.begin(), shapes.end());
     std::ostringstream o;
     const lbvp_ctx* c0 = m[0];
     o << c0->p.storage << '/' << (c0->p.flags & LBVP_LAYOUT_AA) << '/' << c0->p.force_every << '/' << steps << '/'
       << (flags & LBVP_TUNE_LAYOUTS);
-    for (auto& x : shapes) o << ';' << x[0] << 'x' << x[1] << (x[2] ? "m" + std::to_string(x[2]) : "");
+    for (auto& x : shapes) o << ';' << x[0] << 'x' << x[1] << (x[2] ? "m" + std::to_string(x[2]) : "") << (x[3] ? "c" : "");
     return o.str();
 }
 

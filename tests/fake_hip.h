@@ -21,7 +21,7 @@ struct ihipEvent_t {
 
 namespace fake {
 bool no_pinned = false;   // pinned host memory is used up
-int current = 0, launches = 0, host_allocs = 0, host_frees = 0, events = 0, copies = 0;
+int current = 0, launches = 0, host_allocs = 0, host_frees = 0, events = 0, copies = 0, dev_allocs = 0;
 hipError_t last = hipSuccess;
 hipError_t note(hipError_t e)
 {
@@ -110,6 +110,7 @@ hipError_t hipMemcpy2DAsync(void* dst, size_t dp, const void* src, size_t sp, si
 }
 hipError_t hipMalloc(void** p, size_t n)
 {
+    fake::dev_allocs += 1;
     *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
     return *p ? hipSuccess : fake::note(hipErrorOutOfMemory);
 }

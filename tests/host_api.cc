@@ -154,12 +154,41 @@ static int default_shape()
     return 0;
 }
 
+// The tuner's cached rows of a domain are not those of a slab of its size, whose cut
+// keeps it from running two steps a launch, and the other way round.
+static int tune_cuts()
+{
+    ihipStream_t s{0};
+    lbvp_params whole = params(256, 128, LBVP_F32), slab = whole;
+    slab.bc_west = slab.bc_east = LBVP_BC_NEIGHBOR;
+    whole.bc_west = whole.bc_east = LBVP_BC_PERIODIC;
+    slab.force_capacity = whole.force_capacity = 1024;
+    lbvp_ctx *w = nullptr, *c = nullptr;
+    CHECK(lbvp_create(&whole, &s, nullptr, 0, &w) == LBVP_OK);
+    CHECK(lbvp_create(&slab, &s, nullptr, 0, &c) == LBVP_OK);
+    lbvp_tune_row rows[32];
+    auto measures = [&](lbvp_ctx* x) {   // whether the call made scratch contexts
+        int32_t n = 0, best = 0;
+        const int before = fake::dev_allocs;
+        const lbvp_status st = lbvp_tune(&x, 1, 4, 0, rows, 32, &n, &best);
+        if (st != LBVP_OK) std::printf("%s\n", lbvp_tune_last_error());
+        return st != LBVP_OK ? -1 : fake::dev_allocs > before ? 1 : 0;
+    };
+    CHECK(measures(w) == 1);
+    CHECK(measures(c) == 1);
+    CHECK(measures(w) == 0);
+    CHECK(measures(c) == 0);
+    CHECK(lbvp_destroy(w) == LBVP_OK && lbvp_destroy(c) == LBVP_OK);
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
     if (!std::strcmp(what, "pool_staging")) return pool_staging();
     if (!std::strcmp(what, "static_capacity")) return static_capacity();
     if (!std::strcmp(what, "default_shape")) return default_shape();
+    if (!std::strcmp(what, "tune_cuts")) return tune_cuts();
     std::printf("unknown check %s\n", what);
     return 2;
 }
