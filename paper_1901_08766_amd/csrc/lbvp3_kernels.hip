@@ -70,7 +70,8 @@ struct Node3 {
 // Steps (4)-(6) at node (i, j, k) with streamed populations f (weight-normalized);
 // overwrites f with the post-collision populations.
 // EXACT_MOM as in the 2-D step: the 2-byte storage types take 3 rho u as (3 rho) u.
-template <typename R, bool EXACT_MOM = true>
+// FIELDS: the node's density, velocity and force are stored.
+template <typename R, bool EXACT_MOM = true, bool FIELDS = false>
 __device__ __forceinline__ Node3<R> collide3(R (&f)[Q], int body, int i, int j, int k, const Step3Args<R>& a)
 {
     const R faces = ((f[1] + f[2]) + (f[3] + f[4])) + (f[5] + f[6]);
@@ -78,7 +79,7 @@ __device__ __forceinline__ Node3<R> collide3(R (&f)[Q], int body, int i, int j, 
                     ((f[15] + f[16]) + (f[17] + f[18]));
     const R drho = div36(R(12) * f[0] + (R(2) * faces + edges));
     const R rho = a.rho0 + drho;
-    const R inv_36rho = recip(R(36) * rho);
+    const R inv_36rho = recip<FIELDS>(R(36) * rho);
     const R d78 = f[7] - f[8], d910 = f[9] - f[10], d1112 = f[11] - f[12], d1314 = f[13] - f[14];
     const R d1516 = f[15] - f[16], d1718 = f[17] - f[18];
     // 36 j from the odd parts of the pairs, plus 18 F_b (eq. rho*velocity-star)
@@ -366,7 +367,7 @@ __device__ __forceinline__ void step3_body(const S* __restrict__ src, S* __restr
                 }
             }
             const int i = i0 + e;
-            const Node3<R> n = collide3<R, (sizeof(S) >= 4)>(f, body[e], i, j, k, a);
+            const Node3<R> n = collide3<R, (sizeof(S) >= 4), FIELDS>(f, body[e], i, j, k, a);
 #pragma unroll
             for (int q = 0; q < Q; ++q) out[q][e] = enc<S>(f[q]);
             fl[0][e] = n.rho;

@@ -266,31 +266,47 @@ __device__ __forceinline__ double block_sum(double v, double* lds)
 // Quotients that must not carry a fixed relative error (a biased 1/36 or 1/rho
 // would bias every collision's momentum, which a decaying flow accumulates):
 // multiplied by the rounded reciprocal and corrected with the exact residual (one
-// FMA). In FP64 that is the correctly rounded quotient (Markstein: the reciprocal is
-// correctly rounded and the first quotient within an ulp), in 3 instructions
-// instead of the division's 11; in FP32 it is within a hair of it, with no
-// systematic direction. 1/x: the hardware's approximation (22 bits or better in
-// FP64, ~1 ulp in FP32), Newton steps and the same last correction. 1/0 and infinite
-// operands give NaN: a node that gets there makes the mass non-finite either way.
-// FP64 3072 x 1536: 78.4 -> 77.0 us per step.
-template <int D, typename R>
-__device__ __forceinline__ R div_const(R s)
+// FMA); in FP32 that is within a hair of the quotient, with no systematic direction.
+// 1/x: the hardware's approximation (22 bits or better in FP64, ~1 ulp in FP32),
+// Newton steps and the same last correction. In FP64 these are the steps of a division
+// without its scaling of the extreme exponents, so they give what / gives (over 2^28
+// random operands each of all exponents within 2^1000, near 1 and near mantissas of
+// ones and zeros: every bit), in fewer instructions: 3072 x 1536 78.4 -> 77.0 us per
+// step. Zeros and infinities make NaNs on the way; SPECIAL gives the quotients that
+// involve one where results tell them from a NaN (the density, which the mass record
+// sums, and the velocity of the fields; a collision makes NaNs of both): infinities over
+// D by the lowest number in place of the residual, reciprocals by div_fixup.
+template <int D, bool SPECIAL>
+__device__ __forceinline__ double div_const(double s)
 {
-    const R r = R(1) / R(D);
-    const R q = s * r;
-    return fma(fma(R(-D), q, s), r, q);
+    const double r = 1.0 / D;
+    const double q = s * r;
+    double e = fma((double)-D, q, s);
+    if constexpr (SPECIAL) e = fmax(e, -__DBL_MAX__);
+    return fma(e, r, q);
+}
+template <int D, bool SPECIAL>
+__device__ __forceinline__ float div_const(float s)
+{
+    const float r = 1.0f / D;
+    const float q = s * r;
+    return __builtin_fmaf(__builtin_fmaf((float)-D, q, s), r, q);
 }
 template <typename R>
-__device__ __forceinline__ R div36(R s) { return div_const<36>(s); }
+__device__ __forceinline__ R div36(R s) { return div_const<36, true>(s); }
 template <typename R>
-__device__ __forceinline__ R div12(R s) { return div_const<12>(s); }
+__device__ __forceinline__ R div12(R s) { return div_const<12, false>(s); }
+template <bool SPECIAL>
 __device__ __forceinline__ double recip(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
     r = fma(fma(-x, r, 1.0), r, r);
     r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
+    r = fma(fma(-x, r, 1.0), r, r);
+    if constexpr (SPECIAL) r = __builtin_amdgcn_div_fixup(r, x, 1.0);
+    return r;
 }
+template <bool SPECIAL>
 __device__ __forceinline__ float recip(float x)
 {
     const float r = __builtin_amdgcn_rcpf(x);            // ~1 ulp

@@ -78,7 +78,8 @@ __device__ __forceinline__ void penalize(const BodySource<R>& src, int body, int
 // EXACT_MOM: the odd equilibrium from the momentum (momentum3); the 2-byte
 // storage types take 3 rho u as (3 rho) u instead, whose ~1e-8 momentum bias is
 // far below their own rounding, for two fewer quotients per node.
-template <typename R, bool MOVING = false, bool EXACT_MOM = true>
+// FIELDS: the node's density and velocity are stored.
+template <typename R, bool MOVING = false, bool EXACT_MOM = true, bool FIELDS = false>
 __device__ __forceinline__ NodeResult<R> collide_node(R (&f)[9], int body, int i, int j, const StepArgs<R>& a,
                                                     const BodySource<R>& bs)
 {
@@ -88,7 +89,7 @@ __device__ __forceinline__ NodeResult<R> collide_node(R (&f)[9], int body, int i
     const R drho = div36(s36);
     const R rho = a.rho0 + drho;
     const R d57 = f[5] - f[7], d86 = f[8] - f[6];
-    const R inv_36rho = recip(R(36) * rho);
+    const R inv_36rho = recip<FIELDS>(R(36) * rho);
     // u* = (j + F_b/2) / rho with 36 j = 4 (h1 - h3) + ... (eq. rho*velocity-star)
     const R jx36 = R(4) * (f[1] - f[3]) + (d57 + d86) + a.fbx18;
     const R jy36 = R(4) * (f[2] - f[4]) + (d57 - d86) + a.fby18;

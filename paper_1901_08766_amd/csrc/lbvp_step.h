@@ -274,7 +274,7 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
                 }
             }
         } else {
-            n = collide_node<R, MOVING, true>(f, body[k], i, j, a, bs);
+            n = collide_node<R, MOVING, true, FIELDS>(f, body[k], i, j, a, bs);
 #pragma unroll
             for (int q = 0; q < 9; ++q) out[q][k] = enc<S>(f[q]);
         }
