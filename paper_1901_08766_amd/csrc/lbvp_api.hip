@@ -486,22 +486,38 @@ std::vector<char> body_table_bytes(const lbvp_body* bodies, int32_t n, int32_t m
 
 // Whether the context's launch shape is one whose steps run two to a launch
 // (k_march): FP64 or FP32 vector launches of the pull layout with a fixed mask and no
-// slab cut, tiles that are single rows, and more rows of tiles than the chip holds
-// wavefronts of k_march (MARCH_WAVES), so that its chunks have two rows or more. Measured (all stores non-temporal), two
-// steps per launch against one, us per step, recording every step: FP32 8192 x 4096 252 against 385, 3072 x
-// 1536 46.0 against 60.4, 2048 x 1024 24.2 against 29.2; FP64 488 against 782, 78
-// against 115, and 1024 x 1024 25.2 against 28.7. Below the line there is too
-// little to fill the chip: FP32 1024 x 512 12.9 against 9.4. One node per thread
-// loses everywhere (1024 x 512 11.5 against 9.1), and 2-byte storage is bound by its
-// conversions and arithmetic: FP16 8192 x 4096 195 against 203, but BF16 2305 x 1153
-// 30 against 23. An offset within a row has to fit 31 bits.
+// slab cut, tiles that are single rows, and enough nodes. Threads past the rows' ends
+// cost a pair of steps, whose time goes with its rounds of workgroups (18432 wavefronts
+// of 6 rows each), more than a single one, bound by memory; 256-thread blocks more than
+// smaller ones. So the line lies at a number of nodes, in wavefronts of them, that is
+// higher where too little of the tiles' width is filled. Channels with four bodies, every
+// step recorded, us per step with two steps a launch against one, 128 threads:
+//                FP32, tiles filled by                   FP64
+//   wavefronts   51 %        75 %        100 %           51 %        75 %        100 %
+//     4000       19.6  15.8              15.0  12.6      15.3  14.1              13.0  12.5
+//     6000       22.1  20.8  21.0  19.0  17.8  18.5      18.9  19.3  17.3  17.6  15.6  17.8
+//  9000-9500     33.9  30.2  25.2  26.9  25.9  27.3      29.4  29.3  21.2  26.6  22.1  27.7
+//    14000       46.1  46.5  36.3  40.2  31.1  39.0      41.0  48.1  32.3  39.3  32.0  39.1
+// 21000-28000    70.4  86.1  52.3  65.7  59.8  89.2      66.0  88.7  47.5  65.0  57.4  87.4
+// and with 256 threads, 51 % filled, 9500: 43.4 against 29.7 and 31.2 against 28.8,
+// 19400: 67.8 against 69.2 and 59.8 against 67.8. Default shapes: FP32 2048 x 1024 21.3
+// against 24.0, 3072 x 1536 43.0 against 54.9, FP64 1024 x 1024 19.3 against 24.6. One node per thread loses everywhere (1024 x 512 11.5 against 9.1),
+// and 2-byte storage is bound by its conversions and arithmetic: FP16 8192 x 4096 195
+// against 203, but BF16 2305 x 1153 30 against 23. An offset within a row has to fit 31
+// bits.
 bool march_shape(const lbvp_ctx* c)
 {
     const Launch& l = c->launch;
-    return (c->p.storage == LBVP_F64 || c->p.storage == LBVP_F32) && l.vec > 1 && !c->aa() && !c->moving() &&
-           c->p.bc_west != LBVP_BC_NEIGHBOR && c->p.bc_east != LBVP_BC_NEIGHBOR && l.tile_rows == 1 &&
-           c->L.lstride * (int64_t)c->esize() < (int64_t(1) << 30) &&
-           (int64_t)l.n_tiles * (l.block / 64) > MARCH_WAVES;
+    if ((c->p.storage != LBVP_F64 && c->p.storage != LBVP_F32) || l.vec == 1 || c->aa() || c->moving() ||
+        c->p.bc_west == LBVP_BC_NEIGHBOR || c->p.bc_east == LBVP_BC_NEIGHBOR || l.tile_rows != 1 ||
+        c->L.lstride * (int64_t)c->esize() >= (int64_t(1) << 30))
+        return false;
+    struct Line { int64_t least, ragged; int32_t percent; };   // wavefronts of nodes; filled at least, below `ragged`
+    const Line at = c->is_f64() ? (l.block > 128 ? Line{6000, 13300, 80} : Line{6000, 10700, 60})
+                                : (l.block > 128 ? Line{8192, 19000, 90} : Line{8192, 14300, 66});
+    const int64_t waves = (int64_t)c->p.nx * c->p.ny / (64 * l.vec);
+    const bool filled = 100 * (int64_t)c->p.nx >= at.percent * (int64_t)l.tiles_x * l.tile_w;
+    return waves >= (filled ? at.least : at.ragged);
 }
 
 // ... and whether they do: there is room for the partials of four records.

@@ -17,7 +17,7 @@ IO = ("inflow_eq", "outflow_zero_grad", "periodic", "periodic")
 # and even calls, calls of an odd number of pairs, several record phases
 @pytest.mark.parametrize("nx,ny,storage,launch,aa", [(96, 40, "f32", None, False), (96, 40, "f32", None, True),
                                                      (300, 64, "f16", (8, 64), False),
-                                                     (700, 1600, "f32", (4, 128), False)])
+                                                     (1021, 760, "f64", (2, 128), False)])
 @pytest.mark.parametrize("n,every", [(41, 1), (101, 1), (41, 3), (23, 3), (42, 5), (22, 8), (40, 0)])
 def test_repeated_calls_replay(lbvp, nx, ny, storage, launch, aa, n, every):
     p = inputs.random_state_problem(nx, ny, seed=17, n_disks=2, bc=IO, tau_plus=0.7)

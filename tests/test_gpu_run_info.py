@@ -1,7 +1,7 @@
-"""Which kernel a context's steps take (lbvp_get_run_info): two steps a launch, with
-the chunks the bitwise tests of pairs are written for, exactly where the rule puts
-them (FP64 and FP32 vector launches of single-row tiles and more than 3072
-wavefronts, a fixed mask and no cut), and one elsewhere."""
+"""Which kernel a context's steps take (lbvp_get_run_info): two steps a launch exactly
+where the rule puts them (FP64 and FP32 vector launches of single-row tiles with a
+fixed mask and no cut, of enough nodes for how far their tiles' width is filled), and
+one elsewhere."""
 import numpy as np
 import pytest
 
@@ -22,22 +22,24 @@ def _info(lbvp, nx, ny, storage, launch, flags=0, bc=IO, **kw):
     return info[:2]
 
 
-# the grids and launch shapes that the tests of pairs compare with single steps;
-# rows = ceil(wavefronts / 3072), at most 6
+# wavefronts of nodes: nx * ny / (64 vec); rows = ceil(wavefronts of the tiles / 3072), at most 6
 @pytest.mark.parametrize("nx,ny,storage,launch,rows", [
-    (129, 3101, "f32", (4, 64), 2), (129, 3101, "f64", (2, 64), 3), (257, 3077, "f32", (4, 64), 3),
-    (257, 3077, "f64", (2, 128), 5), (515, 1601, "f32", (4, 128), 3), (515, 1601, "f64", (2, 256), 5),
-    (1023, 1551, "f32", (4, 256), 3), (1023, 1551, "f64", (2, 128), 5), (2049, 1031, "f32", (4, 64), 4),
-    (2049, 1031, "f64", (2, 64), 6), (700, 1600, "f32", (4, 128), 3), (640, 1601, "f32", (4, 128), 3),
-    (300, 1600, "f64", (2, 128), 3), (2048, 1153, "f32", (4, 128), 4), (8192, 4096, "f32", None, 6)])
+    (1024, 2048, "f32", None, 3), (8192, 4096, "f32", None, 6), (1030, 2040, "f32", None, 4),   # 67 % filled
+    (1023, 2051, "f32", (4, 256), 3), (2049, 1031, "f32", (4, 64), 4), (2049, 1031, "f64", (2, 64), 6),
+    (1024, 750, "f64", (2, 64), 2), (1024, 751, "f64", (2, 256), 2), (700, 2300, "f64", (2, 128), 5),
+    # half filled: a strip of one column
+    (513, 7201, "f32", (4, 128), 6), (257, 14300, "f32", (4, 64), 6), (1025, 4746, "f32", (4, 256), 6),
+    (257, 5361, "f64", (2, 128), 6), (129, 10700, "f64", (2, 64), 6), (515, 3309, "f64", (2, 256), 6)])
 def test_two_steps_a_launch(lbvp, nx, ny, storage, launch, rows):
     assert _info(lbvp, nx, ny, storage, launch) == (2, rows)
 
 
 @pytest.mark.parametrize("nx,ny,storage,launch,kw", [
-    (256, 3072, "f32", (4, 64), {}),                     # as many wavefronts as the chip holds
+    # a row below the line, full and half filled
+    (1024, 2047, "f32", (4, 64), {}), (1024, 749, "f64", (2, 64), {}), (513, 7136, "f32", (4, 128), {}),
+    (1025, 4745, "f32", (4, 256), {}), (257, 5329, "f64", (2, 128), {}), (515, 3305, "f64", (2, 256), {}),
     (1024, 512, "f32", None, {}),                        # one node per thread
-    (128, 8192, "f32", (4, 64), {}),                     # tiles of two rows
+    (128, 80000, "f32", (4, 64), {}),                    # tiles of two rows
     (2049, 1031, "f16", (4, 64), {}), (2049, 1031, "bf16", (8, 64), {}),
     (2049, 1031, "f32", (4, 64), {"flags": 1}),          # the AA layout
     (2049, 1031, "f32", (1, 64), {"moving": True}),
@@ -45,10 +47,6 @@ def test_two_steps_a_launch(lbvp, nx, ny, storage, launch, rows):
     (2049, 1031, "f32", (4, 64), {"bc": ("neighbor", "outflow_zero_grad", "periodic", "periodic")})])
 def test_one_step_a_launch(lbvp, nx, ny, storage, launch, kw):
     assert _info(lbvp, nx, ny, storage, launch, **kw) == (1, 0)
-
-
-def test_one_row_past_the_line(lbvp):
-    assert _info(lbvp, 256, 3073, "f32", (4, 64)) == (2, 2)
 
 
 def test_partials_that_do_not_fit_four_times(lbvp):
