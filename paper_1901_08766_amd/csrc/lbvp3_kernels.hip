@@ -579,16 +579,22 @@ __device__ __forceinline__ void finalize_run(const Fin3Args& f, int buf, int sta
 }
 
 // Most wavefronts per SIMD of a step kernel. With one node per thread FP32 could run 6
-// or 7 and FP64 5; large grids, bound by memory, lose less to each other's rows with 5
-// and 4: FP32 64 domains in a batch 0.488 -> 0.474 ms per step, 512 x 256 x 256 0.860 ->
-// 0.848, FP64 1.743 -> 1.702. The 2-byte types, bound by the vector unit there, keep
-// what the registers allow (5 domains 23.4 us, 24.1 with 5).
-template <typename S, int V>
-constexpr int MOST_WAVES = sizeof(S) == 8 && V == 1 ? 4 : sizeof(S) == 4 && V == 1 ? 5 : 8;
+// or 7 and FP64 5; grids bound by memory lose less to each other's rows with 5 and 4, us
+// per step with and without the limit: FP32 512 x 256 x 256 852 and 863, 256 x 128 x 128
+// 109.2 and 110.6, 192 x 104 x 104 50.3 and 50.7; FP64 1707 and 1746, 218.6 and 223, 115.1
+// and 116.4, down to 144 x 72 x 72 42.0 and 43.0, and no difference below; batches of 20
+// domains FP64 339 and 344, of 5 88.6 and 90.4, FP32 176 and 176, 39 and 41. A single
+// FP32 domain that the last-level cache holds is not bound by memory, and its few
+// rounds of blocks fill the chip better without the limit (WITHIN_CACHE): 144 x 72 x 72
+// 20.7 and 20.1, 160 x 80 x 80 25.8 and 25.4, 128 x 64 x 64 14.7 and 14.6, 176 x 90 x 90
+// 34.6 and 34.7. The 2-byte types, bound by the vector unit, keep what the registers
+// allow (5 domains 23.4 us, 24.1 with 5).
+template <typename S, int V, bool WITHIN_CACHE>
+constexpr int MOST_WAVES = sizeof(S) == 8 && V == 1 ? 4 : sizeof(S) == 4 && V == 1 && !WITHIN_CACHE ? 5 : 8;
 
 // A step launch, behind the leading blocks that sum earlier records.
-template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V>)))
+template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32, bool WITHIN_CACHE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V, WITHIN_CACHE>)))
 k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith<S>::R> a)
 {
     __shared__ double lds[3 * SLOT_PASS * 4];
@@ -609,7 +615,7 @@ k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith
 // lockstep: one step kind, record flag and partial buffer for all; leading
 // blocks sum the members' earlier records.
 template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V>)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V, false>)))
 k_step3_batch(Batch3Launch b)
 {
     using R = typename Arith<S>::R;
@@ -738,7 +744,7 @@ __global__ void __launch_bounds__(256) k_encode3(S* lat, Conv3Args a)
 
 __global__ void k_zero_i64(int64_t* p) { *p = 0; }
 
-template <typename S, int V, bool OFF32>
+template <typename S, int V, bool OFF32, bool WITHIN_CACHE>
 hipError_t step_off(bool record, bool fields, const S* in, S* out, const Step3Args<typename Arith<S>::R>& a,
                     hipStream_t s)
 {
@@ -747,11 +753,11 @@ hipError_t step_off(bool record, bool fields, const S* in, S* out, const Step3Ar
     const dim3 grid((unsigned)(a.tiles_per_xcd * N_XCD + lead)), block((unsigned)a.block);
     const size_t lds = record ? 3 * (size_t)V * (size_t)a.block * sizeof(R) : 0;
     if (record) {
-        if (fields) hipLaunchKernelGGL((k_step3<S, V, true, true, OFF32>), grid, block, lds, s, in, out, a);
-        else hipLaunchKernelGGL((k_step3<S, V, true, false, OFF32>), grid, block, lds, s, in, out, a);
+        if (fields) hipLaunchKernelGGL((k_step3<S, V, true, true, OFF32, WITHIN_CACHE>), grid, block, lds, s, in, out, a);
+        else hipLaunchKernelGGL((k_step3<S, V, true, false, OFF32, WITHIN_CACHE>), grid, block, lds, s, in, out, a);
     } else {
-        if (fields) hipLaunchKernelGGL((k_step3<S, V, false, true, OFF32>), grid, block, 0, s, in, out, a);
-        else hipLaunchKernelGGL((k_step3<S, V, false, false, OFF32>), grid, block, 0, s, in, out, a);
+        if (fields) hipLaunchKernelGGL((k_step3<S, V, false, true, OFF32, WITHIN_CACHE>), grid, block, 0, s, in, out, a);
+        else hipLaunchKernelGGL((k_step3<S, V, false, false, OFF32, WITHIN_CACHE>), grid, block, 0, s, in, out, a);
     }
     return hipGetLastError();
 }
@@ -760,8 +766,11 @@ template <typename S, int V>
 hipError_t step_v(bool record, bool fields, const S* in, S* out, const Step3Args<typename Arith<S>::R>& a,
                   hipStream_t s)
 {
-    return a.off32 ? step_off<S, V, true>(record, fields, in, out, a, s)
-                   : step_off<S, V, false>(record, fields, in, out, a, s);
+    if constexpr (sizeof(S) == 4 && V == 1) {
+        if (a.off32 && a.keep_tiles >= a.tiles_per_xcd) return step_off<S, V, true, true>(record, fields, in, out, a, s);
+    }
+    return a.off32 ? step_off<S, V, true, false>(record, fields, in, out, a, s)
+                   : step_off<S, V, false, false>(record, fields, in, out, a, s);
 }
 
 template <typename S>
