@@ -378,6 +378,23 @@ uint64_t lattice_bytes(const lbvp_ctx* c)
     return 2 * (uint64_t)c->p.ny * (uint64_t)c->L.lstride * c->esize();
 }
 
+// keep_tiles of a D2Q9 launch of `vec` nodes per thread over `bytes` of lattices. Vector
+// launches of FP32 and 2-byte storage whose lattices are about as large as the XCDs'
+// L2s (32 MB together) store everything non-temporal: what they leave there is written
+// back at the launch's end, when nothing else is left to do. us per step plain and
+// non-temporal, FP32, 4 nodes: 249 x 1058 (18 MB) 6.6 and 6.4, 645 x 564 (25 MB) 7.8 and
+// 7.2, 767 x 608 (32 MB) 7.9 and 6.9, but 464 x 538 (17 MB) the same and 623 x 815 (35
+// MB) 9.2 and 10.1; 2 bytes, 4 nodes: 1440 x 455 (23 MB) 8.0 and 7.4, 1891 x 508 (33 MB)
+// 9.6 and 8.9, 877 x 1233 (37 MB) 10.3 and 11.5; 8 nodes: 550 x 1246 (24 MB) 9.3 and 8.5,
+// 2179 x 559 (42 MB) 12.7 and 11.7, 1740 x 811 (48 MB) 14.2 and 15.7. With one node per
+// thread and in FP64 plain stores win or draw at all these sizes.
+int32_t keep_tiles_2d(uint64_t bytes, int32_t tiles_per_xcd, int32_t storage, int32_t vec)
+{
+    constexpr uint64_t MB = uint64_t(1) << 20;
+    if (storage != LBVP_F64 && vec > 1 && bytes >= 18 * MB && bytes < (vec == 8 ? 44 : 34) * MB) return 0;
+    return keep_tiles(bytes, tiles_per_xcd);
+}
+
 template <typename R>
 void fill_step_args(lbvp_ctx* c, StepArgs<R>& a)
 {
@@ -393,7 +410,7 @@ void fill_step_args(lbvp_ctx* c, StepArgs<R>& a)
     a.tiles_x = l.tiles_x;
     a.n_tiles = l.n_tiles;
     a.tiles_per_xcd = l.tiles_per_xcd;
-    a.keep_tiles = keep_tiles(lattice_bytes(c), l.tiles_per_xcd);
+    a.keep_tiles = keep_tiles_2d(lattice_bytes(c), l.tiles_per_xcd, p.storage, l.vec);
     a.band_log2 = band_log2(l.band);
     a.west = p.bc_west;
     a.east = p.bc_east;
@@ -1050,7 +1067,7 @@ lbvp_status batch_run(lbvp_batch* b, int64_t step0, int64_t k0, int64_t n, bool 
         L.off32 &= c->a32.off32;   // off32 does not depend on the precision
         bytes += lattice_bytes(c);
     }
-    L.keep_tiles = keep_tiles(bytes, b->tiles_per_xcd);
+    L.keep_tiles = keep_tiles_2d(bytes, b->tiles_per_xcd, b->storage, b->vec);
     bool pending = false;
     int32_t pending_buf = 0;
     for (int64_t k = k0; k < k0 + n; ++k) {
