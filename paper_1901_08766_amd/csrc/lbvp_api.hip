@@ -145,15 +145,16 @@ Launch default_launch(int32_t nx, int32_t ny, int32_t storage, uint32_t flags, b
     else if (vec > 1) block = two_byte ? MAX_BLOCK : 128;
     Launch l = make_launch(nx, ny, vec, block);
     // 2-byte vector launches whose lattices fit the last-level cache are bound by the
-    // vector unit and take smaller blocks where that leaves fewer threads past the rows'
-    // ends: 2305 x 1153 with 128 threads for 256 18.5 us per step against 20.0 (BF16)
-    // and 19.5 against 20.9 (FP16), 1030 x 2100 with 64 18.2 against 19.7 (FP16). Larger
-    // ones are bound by memory (FP16 4100 x 2100 57.3 against 53.3), small grids by the
-    // launch (FP32 771 x 389 8.6 against 7.1), and FP64 runs two steps a launch (1100 x
-    // 1000 24.0 against 22.5).
-    const bool cached = 18 * (uint64_t)n * storage_bytes(storage) <= uint64_t(1) << 28;
-    for (int32_t b = block / 2; two_byte && vec > 1 && cached && b >= MIN_BLOCK; b /= 2) {
-        const Launch s = make_launch(nx, ny, vec, b);
+    // vector unit and take 128 threads for 256 where that leaves fewer past the rows'
+    // ends: 2305 x 1171 17.8 us per step against 19.6 (FP16, every step recorded), 1030 x
+    // 2135 17.9 against 20.1, 1030 x 5339 34.8 against 39.4, 3100 x 2096 37.6 against 37.8.
+    // Close to the cache's size the records of more tiles push lattice out of it (2305 x
+    // 3167 51.9 against 46.8, 251 MB), and more so with 64 threads (67.2; 1030 x 3398 27.9
+    // against 24.6 with 128). Larger grids are bound by memory (4100 x 2100 57.3 against
+    // 53.3), small ones by the launch (FP32 771 x 389 8.6 against 7.1).
+    const bool cached = 18 * (uint64_t)n * storage_bytes(storage) <= uint64_t(240) << 20;
+    if (two_byte && vec > 1 && cached && block == MAX_BLOCK) {
+        const Launch s = make_launch(nx, ny, vec, MAX_BLOCK / 2);
         if ((int64_t)s.tiles_x * s.tile_w * 16 < (int64_t)l.tiles_x * l.tile_w * 15) l = s;
     }
     *narrowed = l.block < block;

@@ -182,6 +182,28 @@ static int tune_cuts()
     return 0;
 }
 
+// Default blocks of 2-byte grids: 128 threads for 256 on ragged grids well within the
+// last-level cache, 256 where they pad as little or the lattices come close to its size,
+// never 64 for a grid of this many nodes.
+static int default_blocks()
+{
+    ihipStream_t s{0};
+    struct { int32_t nx, ny, block; } cases[] = {{1030, 2135, 128}, {1100, 5000, 128}, {2305, 2819, 128}, {4110, 1581, 128},
+                                                 {1030, 7087, 256}, {2567, 2891, 256}, {2305, 3167, 256}, {1550, 2258, 256},
+                                                 {2567, 857, 256}, {2048, 1200, 256}, {4100, 2100, 256}};
+    for (int32_t storage : {LBVP_F16_DEV, LBVP_BF16_DEV})
+        for (const auto& k : cases) {
+            const lbvp_params p = params(k.nx, k.ny, storage);
+            lbvp_ctx* c = nullptr;
+            int32_t vec = 0, block = 0;
+            CHECK(lbvp_create(&p, &s, nullptr, 0, &c) == LBVP_OK && lbvp_get_launch(c, &vec, &block) == LBVP_OK);
+            if (vec != 4 || block != k.block) std::printf("%d x %d: (%d, %d)\n", k.nx, k.ny, vec, block);
+            CHECK(vec == 4 && block == k.block);
+            CHECK(lbvp_destroy(c) == LBVP_OK);
+        }
+    return 0;
+}
+
 int main(int argc, char** argv)
 {
     const char* what = argc > 1 ? argv[1] : "";
@@ -189,6 +211,7 @@ int main(int argc, char** argv)
     if (!std::strcmp(what, "static_capacity")) return static_capacity();
     if (!std::strcmp(what, "default_shape")) return default_shape();
     if (!std::strcmp(what, "tune_cuts")) return tune_cuts();
+    if (!std::strcmp(what, "default_blocks")) return default_blocks();
     std::printf("unknown check %s\n", what);
     return 2;
 }

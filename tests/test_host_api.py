@@ -11,6 +11,6 @@ def program(tmp_path_factory):
                             ["lbvp_api.hip", "lbvp_pool.hip", "lbvp_readback.hip"])
 
 
-@pytest.mark.parametrize("check", ["pool_staging", "static_capacity", "default_shape", "tune_cuts"])
+@pytest.mark.parametrize("check", ["pool_staging", "static_capacity", "default_shape", "default_blocks", "tune_cuts"])
 def test_host_side(program, check):
     host_build.run(program, check)
