@@ -37,9 +37,10 @@ COUNTERS_FILE = os.path.join(ROOT, "profiles", "step_kernel_counters.json")
 # per lattice: populations per node, the sources its step kernel is built from,
 # and the committed counter summary of that kernel
 LATTICES = {
-    "d2q9": {"q": 9, "sources": ("lbvp_step.h", "lbvp_march.h", "lbvp_node.h", "lbvp_device.h", "lbvp_internal.h"),
+    "d2q9": {"q": 9, "sources": ("lbvp_step.h", "lbvp_march.h", "lbvp_node.h", "lbvp_device.h", "lbvp_cache.h",
+                                  "lbvp_internal.h"),
              "counters": COUNTERS_FILE},
-    "d3q19": {"q": 19, "sources": ("lbvp3_kernels.hip", "lbvp_device.h", "lbvp3_internal.h"),
+    "d3q19": {"q": 19, "sources": ("lbvp3_kernels.hip", "lbvp_device.h", "lbvp_cache.h", "lbvp3_internal.h"),
               "counters": os.path.join(ROOT, "profiles", "step3_kernel_counters.json")},
 }
 STORAGE_BYTES = {"f64": 8, "f32": 4, "f16": 2, "bf16": 2}
@@ -53,9 +54,9 @@ def kernel_source_hash(lattice: str = "d2q9") -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(storage: str, nodes: int, lattice: str = "d2q9", key: str = None):
-    """HBM bytes per step-kernel launch from the committed rocprofv3 counter
-    summary, if it was taken on the current kernel source; else None."""
+def measured_traffic(storage: str, nodes: int, lattice: str = "d2q9", key: str = None, steps_per_launch: int = 1):
+    """HBM bytes per step from the committed rocprofv3 counter summary, if it was
+    taken on the current kernel source and on launches of as many steps; else None."""
     try:
         with open(LATTICES[lattice]["counters"]) as f:
             c = json.load(f)
@@ -66,7 +67,9 @@ def measured_traffic(storage: str, nodes: int, lattice: str = "d2q9", key: str =
     entry = c.get("per_storage", {}).get(key or storage)
     if not entry or entry.get("nodes") != nodes:
         return None
-    return entry.get("hbm_bytes_per_launch")
+    if entry.get("steps_per_launch", 1) != steps_per_launch:
+        return None
+    return entry["hbm_bytes_per_launch"] // steps_per_launch
 
 
 # the default D2Q9 launch of the 8192 x 4096 domain per storage type (the
@@ -760,6 +763,7 @@ def summarize_counters(step_fetch: str, step_write: str, copy_fetch: str, copy_w
              "fetch_over_algorithmic": round(fetch_b / alg_read, 4),
              "write_over_algorithmic": round(write_b / alg_write, 4)}
     entry["kernel"] = kernel_part
+    entry["steps_per_launch"] = 2 if "k_march" in kernel_part else 1
     entry["command"] = command
     # one entry per storage type, kept while they describe the same kernel source
     try:
@@ -909,7 +913,7 @@ def main():
                     "ms_per_step_runs": [round(x, 4) for x in vruns],
                     "timing": f"median of 5 repeats of {a.steps} steps after {a.warmup} + 100 untimed steps",
                     "achieved_GBps": round(vb, 1), "hbm_frac": round(vb / HBM_PEAK_GBPS, 4), "finite": vok,
-                    "launch": vlaunch, "steps_per_launch": vspl, "traffic": measured_traffic(v, nodes)}
+                    "launch": vlaunch, "steps_per_launch": vspl, "traffic": measured_traffic(v, nodes, steps_per_launch=vspl)}
         print(f"# {v}: {extra[v]}", file=sys.stderr, flush=True)
     if a.moving_storages:
         # the same domain with its masks following the bodies (a cylinder crossing
@@ -926,7 +930,7 @@ def main():
                              "steps_per_launch": vspl, "achieved_GBps": round(vb, 1), "hbm_frac": round(vb / HBM_PEAK_GBPS, 4),
                              "time_vs_fixed_mask": round(vms / fixed, 4) if fixed else None}
             print(f"# moving {v}: {moving_res[v]}", file=sys.stderr, flush=True)
-    traffic = measured_traffic(a.storage, nodes)
+    traffic = measured_traffic(a.storage, nodes, steps_per_launch=spl)
     out = {
         "metric": METRIC,
         "value": round(mlups, 1),

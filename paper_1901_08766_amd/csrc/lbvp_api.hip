@@ -790,17 +790,13 @@ lbvp_status pose_window(lbvp_ctx* c, int64_t next, int64_t n)
     return st;
 }
 
-// The chunks of a two-step launch: as few rows as still let the chip hold all
-// workgroups at once, up to 6, for a chunk of H rows does H + 2 rows of the first
-// step. Above 6 the rows a workgroup takes one after the other cost more than the
-// repeated ones: FP32 8192 x 4096 with H = 4, 6, 8, 16, 32: 257, 252, 254, 276,
-// 309 us per step, FP64 513, 492, 488, 506, -.
+// The chunks of a two-step launch.
 MarchArgs march_args(const lbvp_ctx* c)
 {
     const Launch& l = c->launch;
     const int64_t waves = (int64_t)l.n_tiles * (l.block / 64);
     MarchArgs m{};
-    m.rows = (int32_t)std::min<int64_t>((waves + MARCH_WAVES - 1) / MARCH_WAVES, MARCH_ROWS);
+    m.rows = march_rows(waves);
     m.n_chunks = (c->p.ny + m.rows - 1) / m.rows;
     m.per_xcd = (m.n_chunks * l.tiles_x + N_XCD - 1) / N_XCD;
     m.keep = keep_tiles(lattice_bytes(c), m.per_xcd);

@@ -124,6 +124,15 @@ static_assert(sizeof(StepArgs<double>) <= 544 && sizeof(StepArgs<float>) <= 432 
 // columns, cut into chunks of `rows` rows.
 constexpr int MARCH_ROWS = 6;       // most rows of a chunk
 constexpr int MARCH_WAVES = 3072;   // wavefronts of it the chip holds: 1024 SIMDs, 3 each
+// Rows of a chunk, `waves` wavefronts in a launch of one step: as few as still let the
+// chip hold all workgroups at once, up to 6, for a chunk of H rows does H + 2 rows of the
+// first step. Above 6 the rows a workgroup takes one after the other cost more than the
+// repeated ones: FP32 8192 x 4096 with H = 4, 6, 8, 16, 32: 257, 252, 254, 276, 309 us per
+// step, FP64 513, 492, 488, 506, -.
+constexpr int32_t march_rows(int64_t waves)
+{
+    return waves >= (int64_t)MARCH_ROWS * MARCH_WAVES ? MARCH_ROWS : (int32_t)((waves + MARCH_WAVES - 1) / MARCH_WAVES);
+}
 struct MarchArgs {
     int32_t rows, n_chunks;         // rows per chunk, chunks per strip
     int32_t per_xcd;                // ceil(chunks * strips / 8)
