@@ -12,7 +12,6 @@ namespace lbvp3 {
 
 constexpr int Q = 19;
 constexpr int N_XCD = 8;
-constexpr int FIN_THREADS = 256;
 constexpr int N_SLICES = 32;       // slices a record's partials are summed in, a wavefront each
 constexpr int FIN_BLOCK_WAVES = 4;  // wavefronts of a block of the record kernels
 constexpr int MAX_TILE_BAND = 1 << 16;

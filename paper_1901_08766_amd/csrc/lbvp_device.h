@@ -1,6 +1,6 @@
 // lbvp_device.h -- device building blocks shared by the D2Q9 and D3Q19 step
 // kernels: storage codecs, aligned and one-off vector accesses, deterministic
-// block and record sums, the quotients whose rounding must not drift, the
+// wavefront and record sums, the quotients whose rounding must not drift, the
 // collision of one population pair, and the XCD-aware tile order.
 #pragma once
 
@@ -243,23 +243,6 @@ __device__ __forceinline__ R* dyn_lds()
 {
     extern __shared__ __align__(16) unsigned char lds_dyn[];
     return reinterpret_cast<R*>(lds_dyn);
-}
-
-
-// Sum over the block in a fixed order (deterministic): wavefront shuffles, then
-// the per-wavefront sums in wavefront order. lds holds one double per wavefront
-// and is reused across calls; every thread gets the result.
-__device__ __forceinline__ double block_sum(double v, double* lds)
-{
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const int nw = (int)(blockDim.x >> 6);
-    double s = lds[0];
-    for (int w = 1; w < nw; ++w) s += lds[w];
-    return s;
 }
 
 // ------------------------------------------------------------ the collision --
