@@ -45,13 +45,13 @@ enum Storage : int32_t { ST_F64 = 0, ST_F32 = 1, ST_F16 = 2, ST_BF16 = 3 };
 struct FinalizeArgs {
     int32_t n_bodies, max_bodies, n_mass;   // n_mass: wavefronts of a launch
     int32_t n_buf;                          // a power of two
-    int64_t capacity;
+    int32_t capacity, mass_stride;
     double mass_offset;             // rho0 * nx * ny
     const int32_t* body_slot_ptr;   // [n_bodies + 1]
     const int32_t* body_slots;      // slots of each body in tile order
     const double* slot_force;       // [n_buf][slot_stride / 2][2]
     const double* mass_part;        // [n_buf][mass_stride]
-    int64_t slot_stride, mass_stride;
+    int64_t slot_stride;
     double* ring_force;             // [capacity][max_bodies][2]
     double* ring_mass;              // [capacity]
     int64_t* rec_count;             // [FIN_COUNTERS] records written so far, all equal between launches
@@ -69,6 +69,7 @@ struct StepArgs {
     int32_t fin_buf;    // partial buffer of the first record that leading blocks of the launch sum
     int32_t fin_n;      // how many records they sum (0: none), in consecutive buffers
     int32_t off32;      // a lattice spans fewer than 2^32 bytes: per-lane offsets fit 32 bits
+    int32_t keep_tiles; // how many of each XCD's tiles a pull step stores plain (the rest non-temporal)
     int64_t pitch;      // elements per row of one population, of the mask and of a field
     int64_t plane;      // elements between the rows of populations q and q + 1 (= pitch)
     int64_t lstride;    // elements between lattice rows j and j + 1 (= 9 pitch)
@@ -99,7 +100,6 @@ struct StepArgs {
     void* lat0;                     // batched launches: the domain's lattices and which one is
     void* lat1;                     // current (two-lattice pull; the AA layout uses lat0 only)
     int32_t cur;
-    int32_t keep_tiles; // how many of each XCD's tiles a pull step stores plain (the rest non-temporal)
     FinalizeArgs fin;
     // moving bodies: pose[(row * MAX_MOVING + b) * POSE_STRIDE + k] holds body b's
     // pose at the time level of table row `row`, k = 0..6: cos th, sin th, cx(t),
@@ -117,7 +117,7 @@ struct StepArgs {
 
 // lbvp_batch_step_static keeps both of every member in an array of a fixed size: what
 // they grow by takes members from its callers.
-static_assert(sizeof(StepArgs<double>) <= 544 && sizeof(StepArgs<float>) <= 432 && sizeof(FinalizeArgs) <= 104,
+static_assert(sizeof(StepArgs<double>) <= 544 && sizeof(StepArgs<float>) <= 432 && sizeof(FinalizeArgs) <= 96,
               "fewer members would fit the static array");
 
 // A launch of two steps (k_march): the strips are the launch shape's tile

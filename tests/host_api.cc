@@ -78,12 +78,13 @@ static int pool_staging()
 }
 
 // Members whose tables fill the 4 MiB array of lbvp_batch_step_static: as many as ever
-// fit (648 bytes of arguments a member in FP64, 536 in FP32, a tile and its start), and
+// fit (648 bytes of arguments a member in FP64 and 536 in FP32 at most, a tile and its
+// start), and
 // no more.
 static int static_capacity()
 {
     ihipStream_t s{0};
-    for (const auto& [storage, fit, refused] : {std::array<int, 3>{LBVP_F64, 6390, 6400}, {LBVP_F32, 7700, 7720}}) {
+    for (const auto& [storage, fit, refused] : {std::array<int, 3>{LBVP_F64, 6390, 6480}, {LBVP_F32, 7700, 7840}}) {
         const lbvp_params p = params(3, 3, storage);
         const size_t n = lbvp_footprint_bytes(&p);
         void* mem = nullptr;
