@@ -5,7 +5,8 @@
  * two-relaxation-time collision and the volume-penalization obstacle force of
  * Cui, Wang, Yao, Liu, Yu, "A Coupled Two-relaxation-time Lattice
  * Boltzmann-Volume Penalization method for Flows Past Obstacles" (arXiv
- * 1901.08766). One time step is one fused HIP kernel on the device: pull
+ * 1901.08766). A time step is one pass of a fused HIP kernel on the device, and
+ * two steps share a pass where that is faster (lbvp_get_run_info): pull
  * streaming (eq. streaming), density and intermediate velocity (eqs. rho,
  * rho*velocity-star), the implicit velocity correction and penalization force
  * (eqs. d-V, force-density), the corrected velocity (eq. velocity-r) and the

@@ -592,9 +592,18 @@ __device__ __forceinline__ void finalize_run(const Fin3Args& f, int buf, int sta
 template <typename S, int V, bool WITHIN_CACHE>
 constexpr int MOST_WAVES = sizeof(S) == 8 && V == 1 ? 4 : sizeof(S) == 4 && V == 1 && !WITHIN_CACHE ? 5 : 8;
 
+// ... and the least it has to leave registers for. The 4-node form of the 2-byte types,
+// its loads all in flight, would take 4 registers more than 3 wavefronts have: with 2, us
+// per recorded step against 3, FP16 256 x 128 x 128 62.5 and 57.5, 384 x 160 x 160 170
+// and 142, 640 x 200 x 200 501 and 385, 800 x 300 x 300 1150 and 1003, 512 x 256 x 256
+// 440 and 431 (but 500 x 250 x 250 428 and 455); batches of 8 domains 37.6 and 35.3, of 64
+// 316 and 310. The form that keeps the fields would spill 11 and stays at 2.
+template <typename S, int V, bool FIELDS>
+constexpr int LEAST_WAVES = sizeof(S) == 2 && V == 4 && !FIELDS ? 3 : 1;
+
 // A step launch, behind the leading blocks that sum earlier records.
 template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32, bool WITHIN_CACHE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V, WITHIN_CACHE>)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((LEAST_WAVES<S, V, FIELDS>), MOST_WAVES<S, V, WITHIN_CACHE>)))
 k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith<S>::R> a)
 {
     __shared__ double lds[3 * SLOT_PASS * 4];
@@ -615,7 +624,7 @@ k_step3(const S* __restrict__ src, S* __restrict__ dst, Step3Args<typename Arith
 // lockstep: one step kind, record flag and partial buffer for all; leading
 // blocks sum the members' earlier records.
 template <typename S, int V, bool RECORD, bool FIELDS, bool OFF32>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, MOST_WAVES<S, V, false>)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((LEAST_WAVES<S, V, FIELDS>), MOST_WAVES<S, V, false>)))
 k_step3_batch(Batch3Launch b)
 {
     using R = typename Arith<S>::R;
