@@ -20,11 +20,12 @@
 //
 // What bounds it now is a wavefront's chain of rows (loads, 9 V values of first
 // step, barrier, 9 V of second step, stores) with 3 wavefronts per SIMD to hide it:
-// 142 (FP32) and 146 (FP64) registers, and 9 results of every column in LDS (25 KB
-// per 128 threads). Against single steps, us per step: FP32 3072 x 1536 46.0 for 60.4
-// (42.9 since its stores stay in the cache), at 48 % of the vector unit's rate and half
-// of the memory's; FP64 78 for 115; the 8192 x 4096 five-body domain 232 for 387 and 446
-// for 776. Measured and left out (FP32, against 46.0): the held rows in registers (208
+// 142 (FP32) and 145 (FP64) registers, and 9 results of every column in LDS (25 KB
+// per 128 threads). Against single steps with the same stores, us per step: FP32 3072 x
+// 1536 43.0 for 54.9, at 48 % of the vector unit's rate and half of the memory's; FP64
+// 2305 x 1153 50.3 for 65.0; the 8192 x 4096 five-body domain 232 for 387 and 446 for 776.
+// Measured and left out (FP32 3072 x 1536 with every store non-temporal, against 46.0):
+// the held rows in registers (208
 // of them, 2 wavefronts: 52), loads of the next row ahead of the first step's arithmetic
 // (182 registers: 49), registers cut to 4 wavefronts (54).
 #pragma once
