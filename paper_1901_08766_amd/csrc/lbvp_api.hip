@@ -556,13 +556,13 @@ void place_partials(lbvp_ctx* c, size_t n_slots)
     c->fin.n_buf = 2;
     if (!march_shape(c)) return;
     if (4 * n_mass <= 2 * (int64_t)L.max_waves && 4 * n_force <= 4 * L.slot_cap) {
-        c->fin.mass_stride = (int32_t)n_mass;
+        c->fin.mass_stride = n_mass;
         c->fin.slot_stride = n_force;
         c->fin.n_buf = 4;
     } else if ((size_t)(4 * (n_mass + n_force)) * sizeof(double) <= L.stage_bytes) {
         c->fin.mass_part = c->at<double>(L.stage);
         c->fin.slot_force = c->at<double>(L.stage) + 4 * n_mass;
-        c->fin.mass_stride = (int32_t)n_mass;
+        c->fin.mass_stride = n_mass;
         c->fin.slot_stride = n_force;
         c->fin.n_buf = 4;
     }

@@ -332,7 +332,7 @@ __device__ __forceinline__ void record_tile(const KernelArgs<R>& args, bool on, 
 {
     const auto* a = args.get();
     const int block = a->block, nw = block >> 6;
-    double* mass_part = a->mass_part + (int64_t)buf * a->fin.mass_stride;
+    double* mass_part = a->mass_part + buf * a->fin.mass_stride;
     const int lane = (int)(threadIdx.x & 63), wid = (int)threadIdx.x >> 6;
     const double wm = wave_sum_lane63(drho);
     buffer_store<true>(buffer_at(mass_part + (int64_t)t * nw, (uint32_t)nw * 8), wm,

@@ -407,7 +407,7 @@ __device__ __forceinline__ void step_body(const S* src, S* dst, const StepArgs<t
 
     if constexpr (RECORD) {
         // mass: one partial per wavefront (DPP moves only, no block barrier)
-        double* mass_part = a.mass_part + (int64_t)part_buf * a.fin.mass_stride;
+        double* mass_part = a.mass_part + part_buf * a.fin.mass_stride;
         double* slot_force = a.slot_force + part_buf * a.fin.slot_stride;
         const double wm = wave_sum_lane63(tile_drho);
         if (lane == 63) mass_part[(int64_t)t * (a.block >> 6) + (threadIdx.x >> 6)] = wm;
