@@ -146,12 +146,12 @@ Launch default_launch(int32_t nx, int32_t ny, int32_t storage, uint32_t flags, b
     Launch l = make_launch(nx, ny, vec, block);
     // 2-byte vector launches whose lattices fit the last-level cache are bound by the
     // vector unit and take 128 threads for 256 where that leaves fewer past the rows'
-    // ends: 2305 x 1171 17.8 us per step against 19.6 (FP16, every step recorded), 1030 x
-    // 2135 17.9 against 20.1, 1030 x 5339 34.8 against 39.4, 3100 x 2096 37.6 against 37.8.
+    // ends: 2305 x 1171 17.6 us per step against 19.2 (FP16, every step recorded), 1030 x
+    // 2135 17.4 against 19.7, 1030 x 5339 34.5 against 38.8, 3100 x 2096 37.5 against 37.8.
     // Close to the cache's size the records of more tiles push lattice out of it (2305 x
-    // 3167 51.9 against 46.8, 251 MB), and more so with 64 threads (67.2; 1030 x 3398 27.9
-    // against 24.6 with 128). Larger grids are bound by memory (4100 x 2100 57.3 against
-    // 53.3), small ones by the launch (FP32 771 x 389 8.6 against 7.1).
+    // 3167 51.1 against 45.0, 251 MB), and more so with 64 threads (66.1; 1030 x 3398 27.7
+    // against 24.3 with 128). Larger grids are bound by memory (4100 x 2100 54.9 against
+    // 52.2), small ones by the launch (FP32 771 x 389 8.6 against 7.1).
     const bool cached = 18 * (uint64_t)n * storage_bytes(storage) <= uint64_t(240) << 20;
     if (two_byte && vec > 1 && cached && block == MAX_BLOCK) {
         const Launch s = make_launch(nx, ny, vec, MAX_BLOCK / 2);
@@ -383,12 +383,14 @@ uint64_t lattice_bytes(const lbvp_ctx* c)
 // launches of FP32 and 2-byte storage whose lattices are about as large as the XCDs'
 // L2s (32 MB together) store everything non-temporal: what they leave there is written
 // back at the launch's end, when nothing else is left to do. us per step plain and
-// non-temporal, FP32, 4 nodes: 249 x 1058 (18 MB) 6.6 and 6.4, 645 x 564 (25 MB) 7.8 and
-// 7.2, 767 x 608 (32 MB) 7.9 and 6.9, but 464 x 538 (17 MB) the same and 623 x 815 (35
-// MB) 9.2 and 10.1; 2 bytes, 4 nodes: 1440 x 455 (23 MB) 8.0 and 7.4, 1891 x 508 (33 MB)
-// 9.6 and 8.9, 877 x 1233 (37 MB) 10.3 and 11.5; 8 nodes: 550 x 1246 (24 MB) 9.3 and 8.5,
-// 2179 x 559 (42 MB) 12.7 and 11.7, 1740 x 811 (48 MB) 14.2 and 15.7. With one node per
-// thread and in FP64 plain stores win or draw at all these sizes.
+// non-temporal, 128-thread blocks if not said, FP32, 4 nodes: 249 x 1058 (18 MB) 6.6 and
+// 6.4, 645 x 564 (25 MB) 7.7 and 7.0, 767 x 608 (32 MB) 8.4 and 7.5, but 464 x 538 (17 MB)
+// the same and 623 x 815 (35 MB) 9.4 and 10.6; 2 bytes, 4 nodes: 1440 x 455 (23 MB) 7.9
+// and 7.1, 1891 x 508 (33 MB) 9.8 and 9.0, 877 x 1233 (37 MB) 10.9 and 11.0, with 256
+// threads 10.5 and 11.2; 8 nodes: 550 x 1246 (24 MB) 9.4 and 8.5, 700 x 1600 (39 MB) 12.6
+// and 11.4, 2179 x 559 (42 MB) 12.6 and 11.4 (but 256 threads, half of them idle, 14.9 and
+// 15.3), 1740 x 811 (48 MB) 13.4 and 13.2, with 256 threads 14.1 and 15.0. With one node
+// per thread and in FP64 plain stores win or draw at all these sizes.
 int32_t keep_tiles_2d(uint64_t bytes, int32_t tiles_per_xcd, int32_t storage, int32_t vec)
 {
     constexpr uint64_t MB = uint64_t(1) << 20;
